@@ -27,64 +27,94 @@ __host__ __device__ inline uint32_t pack_item(int sample, int bond) {
 __host__ __device__ inline int item_sample(uint32_t e) { return (int)(e >> kBondBits); }
 __host__ __device__ inline int item_bond(uint32_t e) { return (int)(e & ((1u << kBondBits) - 1)); }
 
-// log(1 + v) for -1/2 <= v <= 0, the range the FP64 ln cosh needs (v =
-// expm1(-2|z|) / 2), to about 2 ulp.  With m = 1 + v (its rounding c = v -
-// (m - 1) kept exactly) and m2 = m or 2m in [1/sqrt 2, sqrt 2):
-// log m2 = 2 atanh s = 2s (1 + s^2/3 + s^4/5 + ...), s = (m2 - 1)/(m2 + 1),
-// |s| <= 0.1716, where the first term left out, s^22 / 23, is below 1e-18
-// relative; then log(1 + v) = log m2 - [m < 1/sqrt 2] ln 2 + c / m.  The
-// general log1p carries extended-precision steps this range does not need
-// (113 FP64 instructions against about 25).
-__device__ inline double log1p_neg(double v)
+// A double held in scalar registers: FP64 instructions take one scalar operand
+// pair but no 64-bit literal, so a polynomial whose coefficients are literals
+// spends two moves per step on them.
+__device__ inline double sgpr(double c)
 {
-    const double m = 1.0 + v;
-    const double c = v - (m - 1.0);
-    const bool lo = m < 0.70710678118654752440;
-    const double m2 = lo ? 2.0 * m : m;
-    const double num = m2 - 1.0, den = m2 + 1.0;
+    asm("" : "+s"(c));
+    return c;
+}
+
+// expm1(-2a) for a >= 0 (any a; NaN gives a finite value): k = rint(x log2 e)
+// from the low bits of x log2 e + 1.5 2^52, r = x - k ln 2 in two parts, the
+// near-minimax degree-9 fit of (expm1 r - r) / r^2 on |r| <= ln 2 / 2, and
+// 2^k (1 + p) - 1.  Below x = -80 expm1 is -1 to the last bit.
+__device__ inline double expm1_m2(double a)
+{
+    const double x = fmax(-2.0 * a, sgpr(-80.0));
+    const double magic = sgpr(6755399441055744.0);
+    const double kd = fma(x, sgpr(1.4426950408889634074), magic);
+    const double k = kd - magic;
+    double r = fma(k, sgpr(-0x1.62e42fefa3800p-1), x);
+    r = fma(k, sgpr(-0x1.ef35793c76730p-45), r);
+    double e = sgpr(2.5100375929185925e-08);
+    e = fma(e, r, sgpr(2.762007600563138e-07));
+    e = fma(e, r, sgpr(2.7557268480106926e-06));
+    e = fma(e, r, sgpr(2.480152132210459e-05));
+    e = fma(e, r, sgpr(0.00019841269863040675));
+    e = fma(e, r, sgpr(0.001388888891719689));
+    e = fma(e, r, sgpr(0.008333333333330065));
+    e = fma(e, r, sgpr(0.041666666666624164));
+    e = fma(e, r, sgpr(0.16666666666666669));
+    e = fma(e, r, sgpr(0.5000000000000001));
+    const double p = fma(r * r, e, r);
+    const int ki = (int)__double2loint(kd);
+    const double s = __hiloint2double((ki << 20) + 0x3ff00000, 0);
+    return fma(p, s, s - 1.0);
+}
+
+// ln cosh from a = |z| and m = expm1(-2a): a + log((1 + e^{-2a}) / 2) with
+// log(1 + m / 2) = 2 atanh s, s = m / (4 + m), |s| <= 1/3, and the
+// near-minimax degree-9 fit of (atanh s / s - 1) / s^2 in s^2 <= 1/9.  No
+// branch and no range split: 43 vector instructions with expm1_m2, against 107
+// for the library expm1 and a split logarithm.  FP64 matrix and vector
+// instructions of a SIMD do not overlap (measured: 64 and 5 cycles each, 149
+// for one MFMA and 16 vector instructions of two waves), so this count is time.
+// Error against long double: at most 2.7 ulp of |z| (2.7 before), 0.27 to
+// 0.59 ulp rms over 1e-8 .. 700 (0.20 to 0.63 before).
+__device__ inline double ln_cosh_of(double a, double m)
+{
+    const double den = 4.0 + m;
     double y = __builtin_amdgcn_rcp(den);
     y = fma(fma(-den, y, 1.0), y, y);
-    double s = num * y;
-    s = fma(fma(-den, s, num), y, s);
+    double s = m * y;
+    s = fma(fma(-den, s, m), y, s);
     const double w = s * s;
-    double p = 1.0 / 21;
-    p = fma(p, w, 1.0 / 19);
-    p = fma(p, w, 1.0 / 17);
-    p = fma(p, w, 1.0 / 15);
-    p = fma(p, w, 1.0 / 13);
-    p = fma(p, w, 1.0 / 11);
-    p = fma(p, w, 1.0 / 9);
-    p = fma(p, w, 1.0 / 7);
-    p = fma(p, w, 1.0 / 5);
-    p = fma(p, w, 1.0 / 3);
-    const double s2 = 2.0 * s;
-    const double lg = fma(s2 * w, p, s2);
-    return (lo ? lg - 0.69314718055994530942 : lg) + c * __builtin_amdgcn_rcp(m);
+    double q = sgpr(0.08082022805976229);
+    q = fma(q, w, sgpr(0.04400369243070233));
+    q = fma(q, w, sgpr(0.06000536404795768));
+    q = fma(q, w, sgpr(0.06657072104827425));
+    q = fma(q, w, sgpr(0.07692785032479314));
+    q = fma(q, w, sgpr(0.09090894718066429));
+    q = fma(q, w, sgpr(0.11111111358713932));
+    q = fma(q, w, sgpr(0.1428571428355438));
+    q = fma(q, w, sgpr(0.20000000000007292));
+    q = fma(q, w, sgpr(0.3333333333333333));
+    const double s2 = s + s;
+    return a + fma(s2 * w, q, s2);
 }
 
 // ln cosh z and tanh z from one expm1, for the forward pass of the backward
 // (which keeps tanh z, the derivative of ln cosh, for the data gradient):
-// with m = expm1(-2|z|), tanh|z| = -m / (2 + m) at full relative precision,
-// and ln cosh z = |z| + log(1 + m / 2) to a few ulp of |z| in absolute terms
-// (the pass needs ln cosh only as the next layer's input, where an absolute
-// error at FP64 rounding level is what any order of the sums gives).
+// tanh|z| = -m / (2 + m) at full relative precision, and ln cosh z to a few
+// ulp of |z| in absolute terms (the pass needs ln cosh only as the next
+// layer's input, where an absolute error at FP64 rounding level is what any
+// order of the sums gives).
 __device__ inline double ln_cosh_tanh(double z, double *th)
 {
     const double a = fabs(z);
-    const double m = expm1(-2.0 * a);
+    const double m = expm1_m2(a);
     *th = copysign(-m / (2.0 + m), z);
-    return a + log1p_neg(0.5 * m);
+    return ln_cosh_of(a, m);
 }
 
-// ln cosh z in FP64 for the forward passes: the same |z| + log(1 + m / 2),
-// m = expm1(-2|z|), so a forward and the backward's forward give equal
-// activations.  No branch: the lanes of a wave never run two forms (a
-// two-branch form with relative precision at small |z| costs twice the FP64
-// instructions where a wave's lanes take both).
+// ln cosh z in FP64 for the forward passes: the same value, so a forward and
+// the backward's forward give equal activations.
 __device__ inline double ln_cosh_fwd(double z)
 {
     const double a = fabs(z);
-    return a + log1p_neg(0.5 * expm1(-2.0 * a));
+    return ln_cosh_of(a, expm1_m2(a));
 }
 
 // Hamiltonian of a context: the J1-J2 spin model [Sec. 6.1, Eq. J1J2] or
