@@ -885,7 +885,7 @@ def main():
             "samples_per_s": nsub / (t64i * 1e-3), "ms": t64i,
             "speedup_vs_full": t64 / t64i,
             "eloc_max_rel_diff_vs_full": float(np.max(np.abs(e64in - e64n)) / np.max(np.abs(e64n))),
-            "cone_kernel": {"name": "k_net_cone64<32>", "bound": "mfma", "ms": ki_ms / max(ki_n, 1),
+            "cone_kernel": {"name": "k_frame64<32>", "bound": "mfma", "ms": ki_ms / max(ki_n, 1),
                             "items": int(b64.shape[0]), "flops": fl64, "tflops": tf64,
                             "frac_fp64_peak": tf64 / PEAK_FP64_TFLOPS,
                             "frac_fp64_sustained": tf64 / SUSTAINED["fp64_tflops"]}}

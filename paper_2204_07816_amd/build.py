@@ -36,7 +36,8 @@ FILE_FLAGS = {
     "calib.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "k_conv_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "k_x3.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
-    "k_net_cone64.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    **{f"k_frame64_{n}.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]
+       for n in ("ln16", "ln32", "cnn1", "cnn2_16", "cnn2_32")},
 }
 
 

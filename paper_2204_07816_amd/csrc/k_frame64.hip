@@ -1,0 +1,144 @@
+// k_frame64.hip -- host side of the FP64 frame form (frame64.h): which networks
+// it serves, the frame and workgroup shape of a launch.
+#include "frame64.h"
+
+namespace nqs {
+
+using namespace frame;
+
+namespace {
+
+void launch_any(const nqs_ctx *c, const FrameArgs &a, bool base, int64_t items, int shape,
+                hipStream_t s)
+{
+    if (c->net == kNetCnn1)
+        launch_cnn1(c, a, base, items, shape, s);
+    else if (c->net == kNetCnn2)
+        (c->C == 32 ? launch_cnn2_32 : launch_cnn2_16)(c, a, base, items, shape, s);
+    else
+        (c->C == 32 ? launch_ln32 : launch_ln16)(c, a, base, items, shape, s);
+}
+
+// The first shape whose waves can form every tile of the largest region at
+// once and of which the LDS holds at least eight waves on a CU (two per SIMD).
+int frame_shape(const nqs_ctx *c, int P, bool regions)
+{
+    const int nhb = c->net == kNetCnn1 ? 1 : c->C / 16;
+    const int wd = regions ? std::min(c->L, 2 + 2 * (c->net == kNetCnn2 ? 2 * c->K : frame_reach(c)))
+                           : c->L;
+    const int T = (wd * wd + 15 - 4 * kQuarters) / 16;
+    const FrameShape *sh = c->C == 16 ? kShapes16 : kShapes32;
+    const int ns = c->C == 16 ? 4 : 3;
+    for (int i = 0; i < ns - 1; ++i) {
+        if (c->net == kNetCnn1 && i == 1) continue;      // (not built: two column blocks per wave)
+        const int g = sh[i].W / nhb;
+        if ((T + g - 1) / g > sh[i].NMAX) continue;
+        if ((int)(kLdsMax / (frame_lds(c, P) * sh[i].PK)) * sh[i].W * sh[i].PK < 8) continue;
+        return i;
+    }
+    return ns - 1;
+}
+
+FrameArgs frame_args(const nqs_ctx *c, const int8_t *spins)
+{
+    FrameArgs a{};
+    a.spins = spins;
+    const int C = c->C;
+    if (c->net == kNetLnCosh) {
+        a.w1 = c->w_vec64;
+        a.w = c->w_vec64 + 10 * C;
+    } else if (c->net == kNetCnn1) {
+        a.w1 = c->w_canon;
+        a.w = c->w_vec64;
+    } else {
+        a.w1 = c->w_canon;
+        a.w = c->w_vec64;
+        a.wf = c->w_canon + 3 * C + (int64_t)c->K * (18 * (int64_t)C * C + 2 * C);
+    }
+    a.err = c->err;
+    a.L = c->L;
+    a.K = c->K;
+    return a;
+}
+
+}  // namespace
+
+bool frame64_ok(const nqs_ctx *c)
+{
+    if (c->dtype != NQS_FP64) return false;
+    if (c->net == kNetCnn1 ? c->C != 16 : (c->C != 16 && c->C != 32)) return false;
+    if (c->net == kNetLnCosh && c->K < 2) return false;
+    return frame_lds(c, c->L) <= kLdsMax;
+}
+
+bool frame64_suits(const nqs_ctx *c)
+{
+    return frame_shape(c, std::min(c->L, 2 * frame_reach(c) + 4), true) < 3;
+}
+
+bool cone64_ok(const nqs_ctx *c)
+{
+    return c->dtype == NQS_FP64 && c->net == kNetLnCosh && (c->C == 16 || c->C == 32) &&
+           c->K >= 2 && c->K <= 8 && c->L >= 2 * c->K + 4;
+}
+
+int64_t frame64_slots(const nqs_ctx *c)
+{
+    return c->net == kNetLnCosh ? c->K - 1 : (c->net == kNetCnn1 ? 2 * c->K - 1 : 2 * c->K);
+}
+
+size_t frame64_cache_bytes(const nqs_ctx *c, int64_t cB)
+{
+    return sizeof(double) * (size_t)frame64_slots(c) * (size_t)cB * c->N * c->C;
+}
+
+// samples per cache fill: at most 16 GiB of cached activations
+int64_t cone64_chunk(const nqs_ctx *c, int64_t B)
+{
+    const int64_t m = (int64_t)(((size_t)16 << 30) / std::max<size_t>(frame64_cache_bytes(c, 1), 1));
+    return std::max<int64_t>(1, std::min(m, std::max<int64_t>(B, 1)));
+}
+
+void frame64_base(const nqs_ctx *c, const int8_t *spins, int64_t cB, int64_t b0, int64_t nb,
+                  double *cache, double *site, int32_t *neg, double *f, int8_t *sgn, hipStream_t s)
+{
+    if (nb <= 0) return;
+    FrameArgs a = frame_args(c, spins);
+    a.cache = cache;
+    a.site = site;
+    a.neg = neg;
+    a.f = f;
+    a.sgn = sgn;
+    a.cB = cB;
+    a.b0 = b0;
+    a.nb = nb;
+    a.P = c->L;
+    launch_any(c, a, true, nb, 0, s);
+}
+
+void frame64_conn(const nqs_ctx *c, const int8_t *spins, const uint32_t *queue,
+                  const int64_t *offsets, int64_t cap, int64_t cB, int64_t b0, int64_t nb,
+                  const double *cache, const double *site, const int32_t *neg, double *dlog,
+                  int8_t *isign, hipStream_t s)
+{
+    if (nb <= 0 || cap <= 0) return;
+    FrameArgs a = frame_args(c, spins);
+    a.queue = queue;
+    a.offsets = offsets;
+    a.cap = cap;
+    a.cache = const_cast<double *>(cache);
+    a.site = const_cast<double *>(site);
+    a.neg = const_cast<int32_t *>(neg);
+    a.cB = cB;
+    a.b0 = b0;
+    a.nb = nb;
+    a.dlog = dlog;
+    a.isign = isign;
+    a.F = frame_reach(c) + 1;
+    a.regions = cache ? 1 : 0;
+    a.P = cache ? std::min(c->L, 2 * a.F + 2) : c->L;
+    const int64_t items = offsets ? cap : nb;
+    launch_any(c, a, false, items, frame_shape(c, a.P, cache != nullptr), s);
+}
+
+}  // namespace nqs

@@ -1,0 +1,12 @@
+#include "frame64.h"
+
+namespace nqs {
+namespace frame {
+
+void launch_ln32(const nqs_ctx *c, const FrameArgs &a, bool base, int64_t items, int shape, hipStream_t s)
+{
+    launch_c<32, kNetLnCosh>(c, a, base, items, shape, s);
+}
+
+}  // namespace frame
+}  // namespace nqs

@@ -256,6 +256,20 @@ nqs_mode resolve_mode(const nqs_ctx *c, nqs_mode m)
     return (inc < 0.7 * full && mfma_inc_supported(c)) ? NQS_INCREMENTAL : NQS_FULL;
 }
 
+// Where a requested mode leads.  `regions`: FULL reached by AUTO on an FP64
+// network whose planes fit the LDS: the neurons that an exchange can change
+// are recomputed and the others taken from the base pass (the same values).
+struct Form {
+    nqs_mode mode;
+    bool regions;
+};
+
+Form resolve_form(const nqs_ctx *c, nqs_mode m)
+{
+    const nqs_mode r = resolve_mode(c, m);
+    return Form{r, m == NQS_AUTO && r == NQS_FULL && frame64_ok(c)};
+}
+
 #define NQS_TRY(x)                        \
     do {                                  \
         nqs_status _s = (x);              \
@@ -341,11 +355,63 @@ nqs_status x3_conn_stage(nqs_ctx *c, const int8_t *spins, nqs_mode mode, double 
     return NQS_OK;
 }
 
+// samples per cache fill of the frame form: at most 4 GiB of activations
+int64_t frame_chunk(const nqs_ctx *c, int64_t B)
+{
+    return std::max<int64_t>(1, std::min<int64_t>(
+                                    (int64_t)(((size_t)4 << 30) / frame64_cache_bytes(c, 1)), B));
+}
+
+nqs_status frame_reserve(nqs_ctx *c, int64_t B, int64_t cap, bool regions, hipStream_t s)
+{
+    Workspace &w = c->ws;
+    NQS_TRY(ensure(w.hsum, sizeof(double) * (size_t)std::max<int64_t>(B, 1) * c->N, s));
+    if (block_net(c)) {
+        NQS_TRY(ensure(w.sgn, std::max<int64_t>(B, 1), s));
+        NQS_TRY(ensure(w.isign, std::max<int64_t>(cap, 1), s));
+        NQS_TRY(ensure(w.hneg, sizeof(int32_t) * (size_t)std::max<int64_t>(B, 1) * c->N, s));
+    }
+    if (regions)
+        NQS_TRY(ensure(w.cache, frame64_cache_bytes(c, frame_chunk(c, std::max<int64_t>(B, 1))), s));
+    return NQS_OK;
+}
+
+// FP64 networks whole in LDS: per chunk of samples the base pass and the
+// chunk's queue items (offsets null: one item per sample).
+nqs_status frame_ratio_stage(nqs_ctx *c, const int8_t *spins, int B, bool regions,
+                             const int64_t *offsets, double *dlog, int64_t cap, hipStream_t s)
+{
+    Workspace &w = c->ws;
+    NQS_TRY(frame_reserve(c, B, cap, regions, s));
+    const int64_t chunk = regions ? frame_chunk(c, B) : B;
+    double *cache = regions ? (double *)w.cache.ptr : nullptr;
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    if (c->timing) {
+        (void)hipEventCreate(&e0);
+        (void)hipEventCreate(&e1);
+    }
+    for (int64_t b0 = 0; b0 < B; b0 += chunk) {
+        const int64_t nb = std::min<int64_t>(chunk, B - b0);
+        frame64_base(c, spins, chunk, b0, nb, cache, (double *)w.hsum.ptr, (int32_t *)w.hneg.ptr,
+                     (double *)w.fbase.ptr, (int8_t *)w.sgn.ptr, s);
+        if (c->timing && b0 == 0) (void)hipEventRecord(e0, s);
+        frame64_conn(c, spins, (const uint32_t *)w.queue.ptr, offsets, cap, chunk, b0, nb, cache,
+                     (const double *)w.hsum.ptr, (const int32_t *)w.hneg.ptr, dlog,
+                     (int8_t *)w.isign.ptr, s);
+    }
+    if (c->timing) {
+        (void)hipEventRecord(e1, s);
+        c->events.push_back({e0, e1});
+    }
+    return NQS_OK;
+}
+
 // Block networks (CNN1, CNN2): base pass (log|psi_net| and sign of the
 // samples), then every queue item recomputed in full: dlog[item] and the
 // sign ratio in ws.isign.
 nqs_status block_ratio_stage(nqs_ctx *c, const BlockNet *bn, const int8_t *spins, int B,
-                             nqs_mode mode, double *dlog, int64_t cap, hipStream_t s)
+                             nqs_mode mode, const int64_t *offsets, double *dlog, int64_t cap,
+                             hipStream_t s)
 {
     Workspace &w = c->ws;
     const bool cone = mode == NQS_INCREMENTAL && incremental_ok(c);
@@ -372,7 +438,13 @@ nqs_status block_ratio_stage(nqs_ctx *c, const BlockNet *bn, const int8_t *spins
         (void)hipEventCreate(&e1);
         (void)hipEventRecord(e0, s);
     }
-    if (cone)
+    if (cone && frame64_suits(c)) {
+        // (the cache ends in the per-site sums and counts of the last layer)
+        const double *cache = (const double *)w.cache.ptr;
+        const double *site = cache + frame64_slots(c) * B * c->N * c->C;
+        frame64_conn(c, spins, (const uint32_t *)w.queue.ptr, offsets, cap, B, 0, B, cache, site,
+                     (const int32_t *)(site + (int64_t)B * c->N), dlog, (int8_t *)w.isign.ptr, s);
+    } else if (cone)
         bn->cone_forward(c, spins, B, (const uint32_t *)w.queue.ptr, (const int64_t *)w.qlen.ptr,
                          cap, (const double *)w.cache.ptr, dlog, (int8_t *)w.isign.ptr, s);
     else
@@ -388,14 +460,18 @@ nqs_status block_ratio_stage(nqs_ctx *c, const BlockNet *bn, const int8_t *spins
     return NQS_OK;
 }
 
-// Base pass + exchanged-configuration pass: dlog[item].
-nqs_status log_ratio_stage(nqs_ctx *c, const int8_t *spins, int B, nqs_mode mode, double *dlog,
-                           int64_t cap, hipStream_t s)
+// Base pass + exchanged-configuration pass: dlog[item].  offsets: the queue
+// offsets of the samples (null: one item per sample).
+nqs_status log_ratio_stage(nqs_ctx *c, const int8_t *spins, int B, Form form,
+                           const int64_t *offsets, double *dlog, int64_t cap, hipStream_t s)
 {
     Workspace &w = c->ws;
+    const nqs_mode mode = form.mode;
     NQS_TRY(ensure(w.fbase, sizeof(double) * std::max(B, 1), s));
+    if (mode == NQS_FULL && frame64_ok(c))
+        return frame_ratio_stage(c, spins, B, form.regions, offsets, dlog, cap, s);
     if (const BlockNet *bn = block_net(c))
-        return block_ratio_stage(c, bn, spins, B, mode, dlog, cap, s);
+        return block_ratio_stage(c, bn, spins, B, mode, offsets, dlog, cap, s);
     NQS_TRY(ensure(w.hsum, sizeof(double) * (size_t)std::max(B, 1) * c->N, s));
     if (c->dtype == NQS_BF16X3) {
         NQS_TRY(bf16_base_stage(c, spins, B, s));
@@ -434,7 +510,7 @@ nqs_status log_ratio_stage(nqs_ctx *c, const int8_t *spins, int B, nqs_mode mode
         // keeps the activations, then the cone over that chunk's queue items
         const int64_t chunk = std::min(vec_chunk(c, B), cone64_chunk(c, B));
         NQS_TRY(ensure(w.plane_a, vec_plane_bytes(c, chunk), s));
-        NQS_TRY(ensure(w.cache, cone64_cache_bytes(c, chunk), s));
+        NQS_TRY(ensure(w.cache, frame64_cache_bytes(c, chunk), s));
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (c->timing) {
             (void)hipEventCreate(&e0);
@@ -446,9 +522,9 @@ nqs_status log_ratio_stage(nqs_ctx *c, const int8_t *spins, int B, nqs_mode mode
                                     (double *)w.hsum.ptr + b0 * c->N, w.plane_a.ptr,
                                     (double *)w.cache.ptr, chunk, s);
             if (c->timing && b0 == 0) (void)hipEventRecord(e0, s);
-            cone64_forward(c, spins, (const uint32_t *)w.queue.ptr, (const int64_t *)w.qlen.ptr,
-                           cap, (const double *)w.cache.ptr, chunk, b0, nb,
-                           (const double *)w.hsum.ptr, dlog, s);
+            frame64_conn(c, spins, (const uint32_t *)w.queue.ptr, offsets, cap, chunk, b0, nb,
+                         (const double *)w.cache.ptr, (const double *)w.hsum.ptr, nullptr, dlog,
+                         nullptr, s);
         }
         if (c->timing) {
             (void)hipEventRecord(e1, s);
@@ -869,8 +945,13 @@ nqs_status nqs_reserve(nqs_ctx *c, int64_t B_max, nqs_mode mode)
     NQS_TRY(ensure(w.dlog, sizeof(double) * std::max<int64_t>(cap, 1), s));
     NQS_TRY(ensure(w.fbase, sizeof(double) * std::max(B, 1), s));
     NQS_TRY(ensure(w.hsum, sizeof(double) * (size_t)std::max(B, 1) * c->N, s));
+    // the frame form serves FULL and AUTO: both reserve its buffers, and the
+    // planes are then those of the amplitudes alone
+    const bool frame = frame64_ok(c);
+    if (frame) NQS_TRY(frame_reserve(c, B, cap, resolve_mode(c, mode) == NQS_FULL, s));
+    const int64_t work = frame ? B : std::max<int64_t>(cap, B);
     if (const BlockNet *bn = block_net(c)) {
-        const int64_t chunk = bn->chunk(c, std::max<int64_t>(cap, B));
+        const int64_t chunk = bn->chunk(c, work);
         NQS_TRY(ensure(w.sgn, std::max(B, 1), s));
         NQS_TRY(ensure(w.isign, std::max<int64_t>(cap, 1), s));
         NQS_TRY(ensure(w.plane_a, bn->plane_bytes(c, chunk), s));
@@ -883,11 +964,11 @@ nqs_status nqs_reserve(nqs_ctx *c, int64_t B_max, nqs_mode mode)
         NQS_TRY(ensure(w.cache, cache_bytes(c, B), s));
         if (resolve_mode(c, mode) == NQS_FULL) NQS_TRY(x3_full_reserve(c, x3_chunk(c, cap), s));
     } else {
-        const int64_t chunk = vec_chunk(c, std::max<int64_t>(cap, B));
+        const int64_t chunk = vec_chunk(c, work);
         NQS_TRY(ensure(w.plane_a, vec_plane_bytes(c, chunk), s));
         NQS_TRY(ensure(w.plane_b, vec_plane_bytes(c, chunk), s));
         if (resolve_mode(c, mode) == NQS_INCREMENTAL && incremental_ok(c))
-            NQS_TRY(ensure(w.cache, cone64_cache_bytes(
+            NQS_TRY(ensure(w.cache, frame64_cache_bytes(
                                         c, std::min(vec_chunk(c, B), cone64_chunk(c, B))), s));
     }
     return NQS_OK;
@@ -939,8 +1020,8 @@ nqs_status nqs_local_energy(nqs_ctx *c, const int8_t *spins, int64_t B, double *
     NQS_TRY(check_common(c, spins, B));
     if (B > 0 && !e_loc) return NQS_E_ARG;
     if (mode != NQS_AUTO && mode != NQS_FULL && mode != NQS_INCREMENTAL) return NQS_E_ARG;
-    const nqs_mode m = resolve_mode(c, mode);
-    if (m == NQS_INCREMENTAL && !incremental_ok(c))
+    const Form m = resolve_form(c, mode);
+    if (m.mode == NQS_INCREMENTAL && !incremental_ok(c))
         return NQS_E_UNSUPPORTED;
     hipStream_t s = (hipStream_t)stream;
     c->last_stream = s;
@@ -948,7 +1029,8 @@ nqs_status nqs_local_energy(nqs_ctx *c, const int8_t *spins, int64_t B, double *
     const int64_t cap = bonds_per_sample(c) * B;
     NQS_TRY(integer_stage(c, spins, (int)B, s));
     NQS_TRY(ensure(c->ws.dlog, sizeof(double) * std::max<int64_t>(cap, 1), s));
-    NQS_TRY(log_ratio_stage(c, spins, (int)B, m, (double *)c->ws.dlog.ptr, cap, s));
+    NQS_TRY(log_ratio_stage(c, spins, (int)B, m, (const int64_t *)c->ws.offsets.ptr,
+                            (double *)c->ws.dlog.ptr, cap, s));
     launch_energy_reduce(c, spins, (int)B, (int64_t *)c->ws.offsets.ptr,
                          (uint32_t *)c->ws.queue.ptr, (double *)c->ws.dlog.ptr,
                          block_net(c) ? (const int8_t *)c->ws.isign.ptr : nullptr,
@@ -963,14 +1045,14 @@ nqs_status nqs_log_ratios(nqs_ctx *c, const int8_t *spins, int64_t B, nqs_mode m
     if (B > 0 && !dlog) return NQS_E_ARG;
     const int64_t cap = bonds_per_sample(c) * B;
     if (capacity < cap) return NQS_E_ARG;
-    const nqs_mode m = resolve_mode(c, mode);
-    if (m == NQS_INCREMENTAL && !incremental_ok(c))
+    const Form m = resolve_form(c, mode);
+    if (m.mode == NQS_INCREMENTAL && !incremental_ok(c))
         return NQS_E_UNSUPPORTED;
     hipStream_t s = (hipStream_t)stream;
     c->last_stream = s;
     if (B == 0) return NQS_OK;
     NQS_TRY(integer_stage(c, spins, (int)B, s));
-    NQS_TRY(log_ratio_stage(c, spins, (int)B, m, dlog, cap, s));
+    NQS_TRY(log_ratio_stage(c, spins, (int)B, m, (const int64_t *)c->ws.offsets.ptr, dlog, cap, s));
     return finish_call();
 }
 
@@ -1073,7 +1155,8 @@ nqs_status nqs_mcmc(nqs_ctx *c, int8_t *spins, int64_t B, int32_t n_steps,
     hipStream_t s = (hipStream_t)stream;
     c->last_stream = s;
     if (B == 0 || n_steps == 0 || bonds_per_sample(c) == 0) return NQS_OK;
-    const nqs_mode m = resolve_mode(c, mode);
+    const Form form = resolve_form(c, mode);
+    const nqs_mode m = form.mode;
     if (m == NQS_INCREMENTAL && c->dtype == NQS_BF16X3 && !incremental_ok(c))
         return NQS_E_UNSUPPORTED;
     Workspace &w = c->ws;
@@ -1101,7 +1184,7 @@ nqs_status nqs_mcmc(nqs_ctx *c, int8_t *spins, int64_t B, int32_t n_steps,
     }
     for (int32_t t = 0; t < n_steps; ++t) {
         launch_mcmc_propose(c, (int)B, rand_bond + (int64_t)t * B, queue, qlen, s);
-        NQS_TRY(log_ratio_stage(c, spins, (int)B, m, dlog, B, s));
+        NQS_TRY(log_ratio_stage(c, spins, (int)B, form, nullptr, dlog, B, s));
         launch_mcmc_decide(c, spins, (int)B, queue, dlog, rand_u + (int64_t)t * B, nullptr,
                            accepted, true, s);
     }
@@ -1196,6 +1279,7 @@ nqs_status time_ratio_forms(nqs_ctx *c, const int8_t *spins, int64_t B, hipStrea
     NQS_TRY(integer_stage(c, spins, (int)B, s));
     NQS_TRY(ensure(c->ws.dlog, sizeof(double) * std::max<int64_t>(cap, 1), s));
     double *dl = (double *)c->ws.dlog.ptr;
+    const int64_t *off = (const int64_t *)c->ws.offsets.ptr;
     hipEvent_t e0, e1;
     HIP_OK(hipEventCreate(&e0));
     HIP_OK(hipEventCreate(&e1));
@@ -1203,10 +1287,10 @@ nqs_status time_ratio_forms(nqs_ctx *c, const int8_t *spins, int64_t B, hipStrea
     const nqs_mode form[2] = {NQS_FULL, NQS_INCREMENTAL};
     nqs_status st = NQS_OK;
     for (int i = 0; i < 2 && st == NQS_OK; ++i) {
-        st = log_ratio_stage(c, spins, (int)B, form[i], dl, cap, s);
+        st = log_ratio_stage(c, spins, (int)B, Form{form[i], false}, off, dl, cap, s);
         if (st != NQS_OK) break;
         (void)hipEventRecord(e0, s);
-        st = log_ratio_stage(c, spins, (int)B, form[i], dl, cap, s);
+        st = log_ratio_stage(c, spins, (int)B, Form{form[i], false}, off, dl, cap, s);
         (void)hipEventRecord(e1, s);
         if (st != NQS_OK) break;
         (void)hipEventSynchronize(e1);

@@ -175,13 +175,14 @@ struct Workspace {
     DevBuf sgn;         // int8 [B] network sign of the samples (CNN1)
     DevBuf isign;       // int8 [capacity] network sign ratio per queue item (CNN1)
     DevBuf hstmp;       // f64 per-site sums of full-recompute chunks (BF16X3)
+    DevBuf hneg;        // int32 [B][N] negative output neurons per site (block networks)
     Graveyard gy;
 
     std::vector<DevBuf *> all()
     {
         return {&counts, &ediag, &offsets, &qlen,  &queue, &dlog,  &fbase,   &hsum,
                 &cache,  &plane_a, &plane_b, &zsave, &hsave, &delta, &sr,    &orows,
-                &counter, &flags, &sgn,    &isign, &hstmp};
+                &counter, &flags, &sgn,    &isign, &hstmp,  &hneg};
     }
     // every buffer files its superseded allocations with this workspace
     void bind()
@@ -283,20 +284,35 @@ void vec_conn_forward(const nqs_ctx *c, const int8_t *spins, const uint32_t *que
                       const int64_t *qlen, int64_t q_begin, int64_t q_count, const double *hsum,
                       double *dlog, void *plane_a, void *plane_b, hipStream_t s);
 size_t vec_plane_bytes(const nqs_ctx *c, int64_t items);
-// FP64 receptive cone of the ln cosh CNN (k_net_cone64.hip): 16 or 32
-// channels, 2 <= K <= 8, L >= 2K + 4.  The base pass of nb samples also keeps
-// h_1 .. h_{K-1} in the cache, [K-1][cB][N][C] (the nb samples at the start
-// of each slot; plane: one plane of nb samples); then one launch gives dlog
-// of the queue items of samples b0 .. b0 + nb - 1 among items 0 .. cap - 1
-// (those samples' activations in the cache, hsum of all samples).
+// FP64 receptive cone of the ln cosh CNN (INCREMENTAL): 16 or 32 channels,
+// 2 <= K <= 8, L >= 2K + 4.  The base pass of nb samples also keeps h_1 ..
+// h_{K-1} in the cache, [K-1][cB][N][C] (the nb samples at the start of each
+// slot; plane: one plane of nb samples); frame64_conn then takes the items.
 bool cone64_ok(const nqs_ctx *c);
-size_t cone64_cache_bytes(const nqs_ctx *c, int64_t cB);
 int64_t cone64_chunk(const nqs_ctx *c, int64_t B);
 void vec_base_forward_cached(const nqs_ctx *c, const int8_t *spins, int nb, double *f,
                              double *hsum, void *plane, double *cache, int64_t cB, hipStream_t s);
-void cone64_forward(const nqs_ctx *c, const int8_t *spins, const uint32_t *queue,
-                    const int64_t *qlen, int64_t cap, const double *cache, int64_t cB, int64_t b0,
-                    int64_t nb, const double *hsum, double *dlog, hipStream_t s);
+// FP64 networks whole in LDS (k_frame64.hip): 16 or 32 channels (CNN1: 16),
+// an L x L frame of the channels within the LDS.  The base pass of samples
+// b0 .. b0 + nb - 1 writes per site the output terms (all samples' [B][N]
+// arrays; neg, sgn: block networks), f, and, unless cache is null, the
+// activations of frame64_slots layers, [slots][cB][N][C].  The exchanged pass
+// gives dlog (and isign) of those samples' queue items (offsets: [B + 1] queue
+// offsets, null: item s belongs to sample s) among items 0 .. cap - 1; with a
+// null cache every neuron is recomputed, else those the exchange can change.
+// frame64_ok: the L x L frame fits (FULL, and AUTO where it resolves to FULL);
+// frame64_suits: CNN1's cone is faster here than in k_c1_cone.
+bool frame64_ok(const nqs_ctx *c);
+bool frame64_suits(const nqs_ctx *c);
+int64_t frame64_slots(const nqs_ctx *c);
+size_t frame64_cache_bytes(const nqs_ctx *c, int64_t cB);
+void frame64_base(const nqs_ctx *c, const int8_t *spins, int64_t cB, int64_t b0, int64_t nb,
+                  double *cache, double *site, int32_t *neg, double *f, int8_t *sgn,
+                  hipStream_t s);
+void frame64_conn(const nqs_ctx *c, const int8_t *spins, const uint32_t *queue,
+                  const int64_t *offsets, int64_t cap, int64_t cB, int64_t b0, int64_t nb,
+                  const double *cache, const double *site, const int32_t *neg, double *dlog,
+                  int8_t *isign, hipStream_t s);
 // Backward: O[B][P] from the saved activations and tanh of the pre-activations.
 // forward of B samples for the backward: tanh z and h = ln cosh z of layers
 // 1..K-1 into zsave / hsave ([layer][B][N][C] FP64 each), and the last

@@ -1,0 +1,74 @@
+"""The FP64 frame form (a configuration's planes in LDS): AUTO, which takes the
+neurons an exchange cannot change from the base pass, against FULL, which
+recomputes them all, and against the oracle, at the edges of its frames (the
+whole torus, the box of the cone, regions clamped in one direction), of its
+tiles (remainders of 0, 2, 4, 8 and 14 sites) and of its workgroup shapes."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2204_07816_amd import inputs, nqs
+
+pytestmark = pytest.mark.gpu
+EPS = 2.0 ** -52
+
+
+def make(net, L, K, C, J2):
+    if net == "cnn1":
+        w = inputs.cnn1_weights(K, C, 0.05, 31, 1.0)
+        return nqs.Context.cnn1(L, 1.0, J2, K, C, w), w, inputs.spins_any(L, 3, 32)
+    if net == "cnn2":
+        w = inputs.cnn2_weights(K, C, 1.0, 31, 2.0)
+        return nqs.Context.cnn2_tj(L, 1.0, 0.4, K, C, w), w, inputs.spins_tj(L, 3, 2 * (L * L // 16), 32)
+    w = inputs.stress_weights(K, C, 1.0, 31)
+    return nqs.Context(L, 1.0, J2, K, C, w), w, inputs.spins_any(L, 3, 32)
+
+
+def energies(net, L, K, C, J2, w, sp):
+    if net == "cnn1":
+        return oracle.cnn1_local_energy(L, 1.0, J2, K, C, w, sp)
+    if net == "cnn2":
+        return oracle.tj_cnn2_local_energy(L, 1.0, 0.4, K, C, w, sp)
+    return oracle.local_energy(L, 1.0, J2, K, C, w, sp)
+
+
+@pytest.mark.parametrize("net,L,K,C,J2", [
+    ("lncosh", 4, 2, 16, 0.5), ("lncosh", 4, 5, 32, 0.5), ("lncosh", 6, 2, 32, 0.0),
+    ("lncosh", 8, 2, 16, 0.5), ("lncosh", 10, 4, 16, 0.5), ("lncosh", 12, 6, 32, 0.5),
+    ("lncosh", 12, 4, 16, 0.5), ("lncosh", 14, 6, 16, 0.5), ("lncosh", 16, 8, 32, 0.0),
+    ("lncosh", 18, 3, 32, 0.5), ("cnn1", 4, 1, 16, 0.5), ("cnn1", 6, 3, 16, 0.0),
+    ("cnn1", 10, 6, 16, 0.5), ("cnn1", 12, 2, 16, 0.5), ("cnn1", 14, 4, 16, 0.5),
+    ("cnn1", 18, 1, 16, 0.5), ("cnn2", 4, 1, 32, 0.0), ("cnn2", 6, 2, 16, 0.0),
+    ("cnn2", 10, 1, 32, 0.0), ("cnn2", 12, 6, 32, 0.0), ("cnn2", 14, 2, 16, 0.0),
+])
+def test_auto_full_and_oracle(net, L, K, C, J2):
+    ctx, w, sp = make(net, L, K, C, J2)
+    spd = torch.as_tensor(sp).cuda()
+    counts, offs, *_ = ctx.connected(spd)
+    n = int(offs[-1])
+    full = ctx.log_ratios(spd, mode="full")[:n].cpu().numpy()
+    auto = ctx.log_ratios(spd, mode="auto")[:n].cpu().numpy()
+    # the same neurons; the two sums over the sites differ by their order, a
+    # few roundings of the largest partial sum (64 at most for these sizes)
+    f = float(ctx.log_psi(spd)[0].abs().max())
+    assert np.max(np.abs(full - auto)) <= 64 * EPS * max(1.0, f)
+    ref = energies(net, L, K, C, J2, w, sp)
+    for mode in ("full", "auto"):
+        e = ctx.local_energy(spd, mode=mode).cpu().numpy()
+        assert np.max(np.abs(e - ref)) <= 1e-10 * np.max(np.abs(ref))
+    assert ctx.get_error() == 0
+
+
+def test_several_cache_fills():
+    """More samples than one fill of the activation cache holds (4 GiB): each
+    sample's energy equals its own call's, bit for bit."""
+    L, K, C = 4, 16, 32
+    w = inputs.stress_weights(K, C, 1.0, 33)
+    sp = torch.as_tensor(inputs.spins_any(L, 512, 34)).cuda()
+    B = 73728                      # 15 layers x 16 sites x 32 channels: 61,440 bytes a sample
+    big = sp.repeat(B // 512, 1, 1).contiguous()
+    ctx = nqs.Context(L, 1.0, 0.5, K, C, w)
+    e = ctx.local_energy(big).reshape(-1, 512)
+    one = ctx.local_energy(sp)
+    assert torch.equal(e, one.expand_as(e))
