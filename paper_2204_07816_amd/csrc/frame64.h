@@ -64,7 +64,18 @@ struct FrameArgs {
     int32_t *err;
     int L, K, P, F, regions;
     int lds;                    // LDS bytes of one configuration
+    // Metropolis chains: the samples' spins are advanced n_steps steps
+    int8_t *chains;             // [B][N]
+    const uint32_t *rnd;        // [n_steps][B]
+    const double *un;           // [n_steps][B]
+    int32_t *accepted;          // [B], added to (may be null)
+    int64_t B;
+    int n_steps, j1, j2;
 };
+
+// what a launch does: exchanged configurations of the queue, the base pass of
+// samples, or Metropolis chains
+constexpr int kItems = 0, kBase = 1, kChains = 2;
 
 __device__ inline int wrap1(int a, int P) { return a < 0 ? a + P : (a >= P ? a - P : a); }
 
@@ -207,11 +218,17 @@ struct Region {
 // such waves, each with its own frame and items and no barrier between them; a
 // workgroup of four puts one on every SIMD, where single-wave workgroups would
 // fill the SIMDs unevenly (11 of 10x10 fit a CU).
-template <int C, int NET, int W, int PK, int NMAX, bool BASE, int EU>
+//
+// Chains: a chain stays with its workgroup for all its steps; its spins and
+// the per-site terms of its configuration live in LDS.  Each proposal whose
+// two spins differ is evaluated in full (the layers in between are not kept),
+// accepted when u < exp(2 dlog), and the terms then replace the chain's.
+template <int C, int NET, int W, int PK, int NMAX, int MODE, int EU>
 __global__ void __launch_bounds__(W * PK * 64, EU)
 k_frame64(FrameArgs a)
 {
     static_assert(PK == 1 || W == 1, "only single waves share a workgroup");
+    constexpr bool BASE = MODE == kBase, CHAIN = MODE == kChains;
     constexpr int NT = W * 64;
     auto sync = [] {
         if constexpr (W == 1) {
@@ -235,12 +252,15 @@ k_frame64(FrameArgs a)
     const int m16 = lane & 15, kq = lane >> 4;
     const int hb = wave % NHB, grp = wave / NHB;
     const int L = a.L, N = L * L, P = a.P, F = a.F, K = a.K;
-    const bool torus = P == L;
+    const bool torus = MODE != kItems || P == L;
     const int SB = plane_bytes16(P);
     int8_t *sf = (int8_t *)(fr + CHK * SB);          // exchanged spins around R_1
     // CNN2, 32 channels: z of the column blocks' first columns; F as [9][C], b
     double *zb = (double *)(fr + CHK * SB + (((P + 2) * (P + 2) + 15) & ~15));
     double *fw = zb + (NET == kNetCnn2 && C == 32 ? 2 * P * P : 0);
+    // chains: per-site terms of the chain's and the proposed configuration, spins
+    double *hs = fw + (NET == kNetCnn2 ? 9 * C + 1 : 0), *hn = hs + N;
+    int8_t *cs = (int8_t *)(hn + N);
     const int S = NET == kNetLnCosh ? K : 2 * K;     // layers stored in the frame
     const int ncache = NET == kNetCnn2 ? S : S - 1;  // of them kept by the base pass
     if constexpr (NET == kNetCnn2) {
@@ -250,10 +270,10 @@ k_frame64(FrameArgs a)
     }
 
     int64_t u, u_end, u_step;
-    if constexpr (BASE) {
-        u = blockIdx.x;
+    if constexpr (MODE != kItems) {
+        u = (int64_t)blockIdx.x * PK + pk;
         u_end = a.nb;
-        u_step = gridDim.x;
+        u_step = (int64_t)gridDim.x * PK;
     } else {
         // the launch's items, split into XCD-contiguous ranges (the grid is a
         // multiple of 8), so that items of one sample share an L2
@@ -265,10 +285,50 @@ k_frame64(FrameArgs a)
         u_end = min(lim, q0 + (xcd + 1) * seg);
         u_step = gridDim.x / kXcd * PK;
     }
-    for (; u < u_end; u += u_step) {
+    // a chain: step -1 evaluates its configuration, then its proposals follow
+    int step = -1, n_acc = 0;
+    uint32_t rnd = 0;
+    double un = 0.0, un_next = 0.0;
+    for (; u < u_end;) {
         int s, qi = -1, qj = -1, ax = 0, ay = 0, w0 = 2, h0 = 2;
-        if constexpr (BASE) {
+        if constexpr (MODE != kItems) {
             s = (int)(a.b0 + u);
+            if constexpr (CHAIN) {
+                auto numbers = [&](int t) {
+                    if (t < a.n_steps) {
+                        rnd = a.rnd[(int64_t)t * a.B + s];
+                        un_next = a.un[(int64_t)t * a.B + s];
+                    }
+                };
+                if (step < 0) {
+                    for (int p = tid; p < N; p += NT) {
+                        cs[p] = a.chains[(int64_t)s * N + p];
+                        hs[p] = 0.0;
+                    }
+                    n_acc = 0;
+                    numbers(0);
+                    sync();
+                } else if (step == a.n_steps) {
+                    for (int p = tid; p < N; p += NT) a.chains[(int64_t)s * N + p] = cs[p];
+                    if (tid == 0 && a.accepted) a.accepted[s] += n_acc;
+                    step = -1;
+                    u += u_step;
+                    sync();
+                    continue;
+                } else {
+                    const int b = proposal_bond(rnd, N, a.j1, a.j2), tau = b & 3;
+                    qi = b >> 2;
+                    const int xi = qi % L, yi = qi / L;
+                    qj = wrap1(yi + bond_dy(tau), L) * L + wrap1(xi + bond_dx(tau), L);
+                    un = un_next;
+                    numbers(step + 1);
+                    // equal spins: S' = S, never accepted
+                    if (__builtin_amdgcn_readfirstlane(cs[qi] == cs[qj])) {
+                        ++step;
+                        continue;
+                    }
+                }
+            }
         } else {
             const uint32_t e = a.queue[u];
             const int b = item_bond(e), tau = b & 3, i0 = b >> 2;
@@ -281,7 +341,7 @@ k_frame64(FrameArgs a)
             w0 = (tau == 1) ? 1 : 2;
             h0 = (tau == 0) ? 1 : 2;
         }
-        const bool part = !BASE && a.regions;
+        const bool part = MODE == kItems && a.regions;
         auto region = [&](int l) {
             Region r{0, 0, L, L};
             if (part) {
@@ -299,8 +359,6 @@ k_frame64(FrameArgs a)
             return y * L + x;
         };
         auto inside = [&](int f) { return f >= P ? f - P : f; };
-        const int8_t *sp = a.spins + (int64_t)s * N;
-
         // the exchanged configuration on R_1 and one site around it, row by row
         // (the wraps of the torus are in the array, so the first layer's
         // neighbours are at constant steps)
@@ -317,7 +375,7 @@ k_frame64(FrameArgs a)
             halo(e, fx, fy);
             int q = site_of(fx, fy);
             q = (q == qi) ? qj : ((q == qj) ? qi : q);
-            sf[e] = sp[q];
+            sf[e] = CHAIN ? cs[q] : a.spins[(int64_t)s * N + q];
         }
         sync();
         // first layer from the spins: CNN2's embedding (R_2: the whole array)
@@ -544,6 +602,9 @@ k_frame64(FrameArgs a)
                 a.site[o] = v;
                 dl += v;
                 if constexpr (NET != kNetLnCosh) a.neg[o] = neg, dn += neg;
+            } else if constexpr (CHAIN) {
+                hn[site] = v;
+                dl += v - hs[site];
             } else {
                 dl += v - a.site[o];
                 if constexpr (NET != kNetLnCosh) dn += neg - a.neg[o];
@@ -621,6 +682,26 @@ k_frame64(FrameArgs a)
             }
         }
         sync();                              // the frame is free again
+        if constexpr (CHAIN) {
+            double v = W > 1 ? 0.0 : dl;
+            if constexpr (W > 1)
+                for (int w = 0; w < W; ++w) v += red[w];
+            if (tid == 0 && !isfinite(v)) atomicOr(a.err, kErrNonFinite);
+            if (__builtin_amdgcn_readfirstlane(step < 0 || un < exp(2.0 * v))) {
+                for (int p = tid; p < N; p += NT) hs[p] = hn[p];
+                if (step >= 0) {
+                    if (tid == 0) {
+                        const int8_t t = cs[qi];
+                        cs[qi] = cs[qj];
+                        cs[qj] = t;
+                    }
+                    ++n_acc;
+                }
+                sync();
+            }
+            ++step;
+            continue;
+        }
         if (tid == 0) {
             double v = W > 1 ? 0.0 : dl;
             int ng = W > 1 ? 0 : dn;
@@ -639,13 +720,15 @@ k_frame64(FrameArgs a)
                 if constexpr (NET != kNetLnCosh) a.isign[u] = sg;
             }
         }
+        u += u_step;
     }
 }
 
-inline size_t frame_lds(const nqs_ctx *c, int P)
+inline size_t frame_lds(const nqs_ctx *c, int P, bool chains = false)
 {
     size_t n = (size_t)(c->C / 2) * plane_bytes16(P) + (size_t)(((P + 2) * (P + 2) + 15) & ~15);
     if (c->net == kNetCnn2) n += sizeof(double) * ((c->C == 32 ? 2 * (size_t)P * P : 0) + 9 * c->C + 1);
+    if (chains) n += (size_t)c->N * (2 * sizeof(double) + 1);
     return (n + 15) & ~(size_t)15;
 }
 
@@ -657,53 +740,65 @@ inline int frame_reach(const nqs_ctx *c)
     return c->net == kNetLnCosh ? c->K : (c->net == kNetCnn1 ? 2 * c->K : 2 * c->K + 1);
 }
 
-template <int C, int NET, int W, int PK, int NMAX, bool BASE, int EU>
+template <int C, int NET, int W, int PK, int NMAX, int MODE, int EU>
 void launch_w(const nqs_ctx *c, FrameArgs a, int64_t items, hipStream_t s)
 {
-    const auto kernel = k_frame64<C, NET, W, PK, NMAX, BASE, EU>;
-    a.lds = (int)frame_lds(c, a.P);
+    const auto kernel = k_frame64<C, NET, W, PK, NMAX, MODE, EU>;
+    a.lds = (int)frame_lds(c, a.P, MODE == kChains);
     const int lds = a.lds * PK;
     (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     int occ = 1;
     (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, W * PK * 64, lds);
     int64_t grid = (int64_t)std::max(occ, 1) * std::max(c->n_cu, 1);
     grid = std::max<int64_t>(1, std::min(grid, (items + PK - 1) / PK));
-    if (!BASE) grid = (grid + kXcd - 1) / kXcd * kXcd;
+    if (MODE == kItems) grid = (grid + kXcd - 1) / kXcd * kXcd;
     NQS_LAUNCH(kernel, dim3((unsigned)grid), dim3(W * PK * 64), lds, s, a);
 }
 
-// Workgroup shapes of the exchanged pass: waves per configuration, configurations
-// per workgroup, tiles a wave can form at once.  The base pass runs the last.
+// Workgroup shapes of the exchanged pass and of chains: waves per
+// configuration, configurations per workgroup, tiles a wave can form at once.
+// The base pass runs the last.
 struct FrameShape {
     int W, PK, NMAX;
 };
 constexpr FrameShape kShapes16[4] = {{1, 4, 7}, {1, 4, 10}, {4, 1, 5}, {8, 1, 10}};
 constexpr FrameShape kShapes32[3] = {{4, 1, 5}, {4, 1, 8}, {8, 1, 10}};
 
-template <int C, int NET>
-void launch_c(const nqs_ctx *c, const FrameArgs &a, bool base, int64_t items, int shape,
-              hipStream_t s)
+template <int C, int NET, int MODE>
+void launch_m(const nqs_ctx *c, const FrameArgs &a, int64_t items, int shape, hipStream_t s)
 {
-    if (base) return launch_w<C, NET, 8, 1, 10, true, 2>(c, a, items, s);
     if constexpr (C == 16) {
         constexpr int EU = NET == kNetCnn1 ? 2 : 3;
-        if (shape == 0) return launch_w<C, NET, 1, 4, 7, false, EU>(c, a, items, s);
-        if constexpr (NET != kNetCnn1)
-            if (shape == 1) return launch_w<C, NET, 1, 4, 10, false, 2>(c, a, items, s);
-        if (shape == 2) return launch_w<C, NET, 4, 1, 5, false, EU>(c, a, items, s);
+        if (shape == 0) return launch_w<C, NET, 1, 4, 7, MODE, EU>(c, a, items, s);
+        if constexpr (NET != kNetCnn1 && MODE == kItems)
+            if (shape == 1) return launch_w<C, NET, 1, 4, 10, MODE, 2>(c, a, items, s);
+        if (shape == 2) return launch_w<C, NET, 4, 1, 5, MODE, EU>(c, a, items, s);
     } else {
-        if (shape == 0) return launch_w<C, NET, 4, 1, 5, false, 3>(c, a, items, s);
-        if (shape == 1) return launch_w<C, NET, 4, 1, 8, false, 2>(c, a, items, s);
+        if (shape == 0) return launch_w<C, NET, 4, 1, 5, MODE, 3>(c, a, items, s);
+        if constexpr (MODE == kItems)
+            if (shape == 1) return launch_w<C, NET, 4, 1, 8, MODE, 2>(c, a, items, s);
     }
-    launch_w<C, NET, 8, 1, 10, false, 2>(c, a, items, s);
+    launch_w<C, NET, 8, 1, 10, MODE, 2>(c, a, items, s);
+}
+
+template <int C, int NET>
+void launch_c(const nqs_ctx *c, const FrameArgs &a, int mode, int64_t items, int shape,
+              hipStream_t s)
+{
+    if (mode == kBase)
+        launch_w<C, NET, 8, 1, 10, kBase, 2>(c, a, items, s);
+    else if (mode == kChains)
+        launch_m<C, NET, kChains>(c, a, items, shape, s);
+    else
+        launch_m<C, NET, kItems>(c, a, items, shape, s);
 }
 
 // one translation unit per network (k_frame64_*.hip)
-void launch_ln16(const nqs_ctx *c, const FrameArgs &a, bool base, int64_t items, int shape, hipStream_t s);
-void launch_ln32(const nqs_ctx *c, const FrameArgs &a, bool base, int64_t items, int shape, hipStream_t s);
-void launch_cnn1(const nqs_ctx *c, const FrameArgs &a, bool base, int64_t items, int shape, hipStream_t s);
-void launch_cnn2_16(const nqs_ctx *c, const FrameArgs &a, bool base, int64_t items, int shape, hipStream_t s);
-void launch_cnn2_32(const nqs_ctx *c, const FrameArgs &a, bool base, int64_t items, int shape, hipStream_t s);
+void launch_ln16(const nqs_ctx *c, const FrameArgs &a, int mode, int64_t items, int shape, hipStream_t s);
+void launch_ln32(const nqs_ctx *c, const FrameArgs &a, int mode, int64_t items, int shape, hipStream_t s);
+void launch_cnn1(const nqs_ctx *c, const FrameArgs &a, int mode, int64_t items, int shape, hipStream_t s);
+void launch_cnn2_16(const nqs_ctx *c, const FrameArgs &a, int mode, int64_t items, int shape, hipStream_t s);
+void launch_cnn2_32(const nqs_ctx *c, const FrameArgs &a, int mode, int64_t items, int shape, hipStream_t s);
 
 }  // namespace frame
 }  // namespace nqs

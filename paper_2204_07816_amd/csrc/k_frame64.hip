@@ -8,15 +8,15 @@ using namespace frame;
 
 namespace {
 
-void launch_any(const nqs_ctx *c, const FrameArgs &a, bool base, int64_t items, int shape,
+void launch_any(const nqs_ctx *c, const FrameArgs &a, int mode, int64_t items, int shape,
                 hipStream_t s)
 {
     if (c->net == kNetCnn1)
-        launch_cnn1(c, a, base, items, shape, s);
+        launch_cnn1(c, a, mode, items, shape, s);
     else if (c->net == kNetCnn2)
-        (c->C == 32 ? launch_cnn2_32 : launch_cnn2_16)(c, a, base, items, shape, s);
+        (c->C == 32 ? launch_cnn2_32 : launch_cnn2_16)(c, a, mode, items, shape, s);
     else
-        (c->C == 32 ? launch_ln32 : launch_ln16)(c, a, base, items, shape, s);
+        (c->C == 32 ? launch_ln32 : launch_ln16)(c, a, mode, items, shape, s);
 }
 
 // The first shape whose waves can form every tile of the largest region at
@@ -113,7 +113,7 @@ void frame64_base(const nqs_ctx *c, const int8_t *spins, int64_t cB, int64_t b0,
     a.b0 = b0;
     a.nb = nb;
     a.P = c->L;
-    launch_any(c, a, true, nb, 0, s);
+    launch_any(c, a, kBase, nb, 0, s);
 }
 
 void frame64_conn(const nqs_ctx *c, const int8_t *spins, const uint32_t *queue,
@@ -138,7 +138,41 @@ void frame64_conn(const nqs_ctx *c, const int8_t *spins, const uint32_t *queue,
     a.regions = cache ? 1 : 0;
     a.P = cache ? std::min(c->L, 2 * a.F + 2) : c->L;
     const int64_t items = offsets ? cap : nb;
-    launch_any(c, a, false, items, frame_shape(c, a.P, cache != nullptr), s);
+    launch_any(c, a, kItems, items, frame_shape(c, a.P, cache != nullptr), s);
+}
+
+bool frame64_chains_ok(const nqs_ctx *c)
+{
+    return frame64_ok(c) && frame_lds(c, c->L, true) <= kLdsMax;
+}
+
+void frame64_chains(const nqs_ctx *c, int8_t *spins, int64_t B, int n_steps, const uint32_t *rnd,
+                    const double *un, int32_t *accepted, hipStream_t s)
+{
+    if (B <= 0 || n_steps <= 0) return;
+    FrameArgs a = frame_args(c, spins);
+    a.chains = spins;
+    a.rnd = rnd;
+    a.un = un;
+    a.accepted = accepted;
+    a.B = a.nb = B;
+    a.n_steps = n_steps;
+    a.j1 = nn_moves(c) ? 1 : 0;
+    a.j2 = nnn_moves(c) ? 1 : 0;
+    a.P = c->L;
+    // A chain is a serial run of steps: four waves share each (10x10, 4 layers
+    // of 16, 32 steps of 512 chains: 0.65 ms against 1.17 for one wave and 0.82
+    // for eight) while their tiles allow; one wave each where the chains alone
+    // fill three waves per SIMD (4096 chains: 3.25 against 3.54 ms).
+    const int T = (c->N + 15 - 4 * kQuarters) / 16;
+    int shape = 3;
+    if (c->C == 16 && T <= kShapes16[0].NMAX && B >= 12 * (int64_t)c->n_cu)
+        shape = 0;
+    else if (c->C == 16 && T <= 4 * kShapes16[2].NMAX)
+        shape = 2;
+    else if (c->C == 32 && T <= 2 * kShapes32[0].NMAX)
+        shape = 0;
+    launch_any(c, a, kChains, B, shape, s);
 }
 
 }  // namespace nqs

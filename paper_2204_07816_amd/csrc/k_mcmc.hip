@@ -11,6 +11,8 @@
 //   accept:  a pair of different values (antiparallel spins; t-J also an
 //            electron and a hole) is exchanged when u < exp(2 (f(S') - f(S))),
 //            u the caller's uniform number in [0, 1).
+// FP64 networks whose planes fit the LDS run all their steps in one launch
+// (k_frame64.hip); what follows serves the others.
 // Where the incremental cone kernel serves, the base pass is taken once and
 // then kept current: accepted chains run a write-back pass of the cone kernel
 // (their cone's activations and site sums replace the cached ones, which is
@@ -25,18 +27,6 @@ namespace nqs {
 namespace {
 
 constexpr int kThreads = 256;
-
-// Bond id of proposal r: r mod (N * ntypes) = site * ntypes + type index,
-// types {0, 1} (nearest neighbours) and/or {2, 3} (next-nearest) as the
-// bonds of each class carry terms (t-J: nearest neighbours only).
-__device__ __host__ inline int proposal_bond(uint32_t r, int N, int j1, int j2)
-{
-    const int ntypes = 2 * (j1 + j2);
-    const int q = (int)(r % (uint32_t)(N * ntypes));
-    const int i = q / ntypes, k = q - i * ntypes;
-    const int t = j1 ? k : 2 + k;
-    return 4 * i + t;
-}
 
 __global__ void __launch_bounds__(kThreads)
 k_mcmc_propose(const uint32_t *__restrict__ rnd, int B, int N, int j1, int j2,

@@ -1159,6 +1159,11 @@ nqs_status nqs_mcmc(nqs_ctx *c, int8_t *spins, int64_t B, int32_t n_steps,
     const nqs_mode m = form.mode;
     if (m == NQS_INCREMENTAL && c->dtype == NQS_BF16X3 && !incremental_ok(c))
         return NQS_E_UNSUPPORTED;
+    if (frame64_chains_ok(c)) {
+        // FP64: every step in one launch (the forms give the same ratios)
+        frame64_chains(c, spins, B, n_steps, rand_bond, rand_u, accepted, s);
+        return finish_call();
+    }
     Workspace &w = c->ws;
     NQS_TRY(ensure(w.queue, sizeof(uint32_t) * B, s));
     NQS_TRY(ensure(w.qlen, sizeof(int64_t) * 4, s));

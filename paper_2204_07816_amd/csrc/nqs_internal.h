@@ -19,6 +19,18 @@ namespace nqs {
 __host__ __device__ inline int bond_dx(int t) { return (t == 1) ? 0 : 1; }
 __host__ __device__ inline int bond_dy(int t) { return t == 0 ? 0 : (t == 1 ? 1 : (t == 2 ? 1 : -1)); }
 
+// Bond id of proposal r: r mod (N * ntypes) = site * ntypes + type index,
+// types {0, 1} (nearest neighbours) and/or {2, 3} (next-nearest) as the
+// bonds of each class carry terms (t-J: nearest neighbours only).
+__host__ __device__ inline int proposal_bond(uint32_t r, int N, int j1, int j2)
+{
+    const int ntypes = 2 * (j1 + j2);
+    const int q = (int)(r % (uint32_t)(N * ntypes));
+    const int i = q / ntypes, k = q - i * ntypes;
+    const int t = j1 ? k : 2 + k;
+    return 4 * i + t;
+}
+
 // Queue entry: sample index and bond id packed in 32 bits (bond < 2^14).
 constexpr int kBondBits = 14;
 __host__ __device__ inline uint32_t pack_item(int sample, int bond) {
@@ -313,6 +325,10 @@ void frame64_conn(const nqs_ctx *c, const int8_t *spins, const uint32_t *queue,
                   const int64_t *offsets, int64_t cap, int64_t cB, int64_t b0, int64_t nb,
                   const double *cache, const double *site, const int32_t *neg, double *dlog,
                   int8_t *isign, hipStream_t s);
+// n_steps Metropolis steps of B chains, one launch (rnd, un: [n_steps][B])
+bool frame64_chains_ok(const nqs_ctx *c);
+void frame64_chains(const nqs_ctx *c, int8_t *spins, int64_t B, int n_steps, const uint32_t *rnd,
+                    const double *un, int32_t *accepted, hipStream_t s);
 // Backward: O[B][P] from the saved activations and tanh of the pre-activations.
 // forward of B samples for the backward: tanh z and h = ln cosh z of layers
 // 1..K-1 into zsave / hsave ([layer][B][N][C] FP64 each), and the last

@@ -72,3 +72,22 @@ def test_several_cache_fills():
     e = ctx.local_energy(big).reshape(-1, 512)
     one = ctx.local_energy(sp)
     assert torch.equal(e, one.expand_as(e))
+
+
+@pytest.mark.parametrize("L,K,C,B,steps", [
+    (4, 2, 16, 5, 7), (4, 2, 16, 3079, 3), (10, 3, 16, 3, 9), (12, 2, 32, 3, 8), (14, 2, 32, 2, 6),
+    (18, 2, 16, 2, 6), (20, 2, 16, 2, 5),
+])
+def test_chains_equal_the_oracle(L, K, C, B, steps):
+    """All steps of a chain in one launch, in every workgroup shape: one wave
+    per chain (many chains), four, and eight."""
+    w = inputs.stress_weights(K, C, 1.0, 41)
+    sp = inputs.spins_sz0(L, B, 42)
+    rb, ru = inputs.mcmc_randoms(43, 0, steps, B)
+    want, acc = oracle.mcmc(L, 1.0, 0.5, K, C, w, sp, rb, ru)
+    ctx = nqs.Context(L, 1.0, 0.5, K, C, w)
+    spd = torch.as_tensor(sp.copy()).cuda()
+    got = ctx.mcmc(spd, torch.as_tensor(rb).cuda(), torch.as_tensor(ru).cuda())
+    assert np.array_equal(spd.cpu().numpy(), want)
+    assert np.array_equal(got.cpu().numpy(), acc)
+    assert ctx.get_error() == 0
