@@ -38,6 +38,7 @@ FILE_FLAGS = {
     "k_x3.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     **{f"k_frame64_{n}.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]
        for n in ("ln16", "ln32", "cnn1", "cnn2_16", "cnn2_32")},
+    **{f"k_frame32_{n}.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"] for n in ("ln16", "ln32")},
 }
 
 

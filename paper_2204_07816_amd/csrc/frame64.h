@@ -37,6 +37,44 @@ namespace nqs {
 namespace frame {
 
 typedef double double4_t __attribute__((ext_vector_type(4)));
+typedef float float4_t __attribute__((ext_vector_type(4)));
+
+// Element type of the frame: 16-byte chunks of VEC channels of a site, the
+// accumulators of v_mfma_*_16x16x4 (element i of lane group kq is row row(kq,
+// i)), and the order of the channels.  FP64: K-step s of a 16-channel block is
+// channels 4 kq + s, a lane's four in two chunks of natural order.  FP32:
+// K-step s is channels 4 s + kq, so that the chain runs over the channels in
+// ascending order: v_mfma_f32_16x16x4f32 adds its four products one by one
+// with a fused multiply-add each (checked against fmaf chains on random
+// operands), which makes every neuron equal the vector kernels' bit for bit;
+// a lane's four sit in one chunk, channel c of a block in chunk c % 4, place c / 4.
+template <typename T> struct Prec;
+template <> struct Prec<double> {
+    static constexpr int VEC = 2, KQ = 1;
+    typedef double2 Chunk;
+    typedef double4_t Acc;
+    static __device__ inline int row(int kq, int i) { return kq + 4 * i; }
+    static __device__ inline int plane(int ch) { return ch >> 1; }
+    static __device__ inline int place(int ch) { return (ch & 1) * 8; }
+    static constexpr int LANE_CH = 4, STEP_CH = 1;       // channel = LANE_CH kq + STEP_CH s
+    static __device__ inline Acc mfma(double a, double b, Acc c)
+    {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+};
+template <> struct Prec<float> {
+    static constexpr int VEC = 4, KQ = 0;
+    typedef float4 Chunk;
+    typedef float4_t Acc;
+    static __device__ inline int row(int kq, int i) { return 4 * kq + i; }
+    static __device__ inline int plane(int ch) { return (ch >> 4) * 4 + (ch & 3); }
+    static __device__ inline int place(int ch) { return ((ch >> 2) & 3) * 4; }
+    static constexpr int LANE_CH = 1, STEP_CH = 4;
+    static __device__ inline Acc mfma(float a, float b, Acc c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+};
 
 constexpr int kXcd = 8;
 // CNN1's packed taps (16 channels): convolution, transposed convolution,
@@ -49,11 +87,11 @@ struct FrameArgs {
     const uint32_t *queue;      // exchanged configurations, or
     const int64_t *offsets;     // [B + 1] queue offsets of the samples (null: one item per sample)
     int64_t cap;
-    const double *w;            // packed taps of the network
-    const double *w1;           // first layer: [9][C], bias (ln cosh); canonical W [32][9], a[32]
+    const void *w;              // packed taps of the network (double or float)
+    const void *w1;             // first layer: [9][C], bias (ln cosh); canonical W [32][9], a[32]
                                 // (CNN1); E [3][C] (CNN2)
     const double *wf;           // CNN2: F [C][9], b
-    double *cache;              // [slots][cB][N][C] of samples b0 ..
+    void *cache;                // [slots][cB][N][C] of samples b0 .., in the frame's chunks
     double *site;               // [B][N] per-site terms of the samples
     int32_t *neg;               // [B][N] negative output neurons per site (block networks)
     double *f;                  // base pass: [B] log-amplitude
@@ -106,7 +144,7 @@ struct TileSite {
     int org, up, dn, lf, rt, to;
 };
 
-constexpr int kQuarters = 1;
+constexpr int kQuarters = 1;         // room for quarter tiles (FP64)
 
 // Accumulators of N tiles of 16 sites (NH column blocks each), of which the
 // last is formed only when `last`, and of nq <= kQuarters quarter tiles of 4
@@ -117,26 +155,29 @@ constexpr int kQuarters = 1;
 // wp: this lane's first weight.  Each K-block's weights are fetched while the
 // previous block's MFMAs issue, and each tile's A operands while the previous
 // tile's do.
-template <int N, int CIN, int COUT, int NH>
+template <typename T, int N, int CIN, int COUT, int NH>
 __device__ __forceinline__ void conv_tiles(const unsigned char *fr, int SB, bool last, int nq,
                                            const TileSite (&st)[N], const TileSite (&sq)[kQuarters],
-                                           const double *wp, const double *bias,
-                                           double4_t (&acc)[N][NH], double (&accq)[kQuarters][NH])
+                                           const T *wp, const T *bias,
+                                           typename Prec<T>::Acc (&acc)[N][NH], T (&accq)[kQuarters][NH])
 {
+    using Pr = Prec<T>;
+    using Chunk = typename Pr::Chunk;
+    constexpr int WS = Pr::STEP_CH * COUT;       // weights of successive K-steps
     constexpr int NCB = CIN / 16;
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
-        const double b = bias[16 * h];
+        const T b = bias[16 * h];
 #pragma unroll
-        for (int j = 0; j < N; ++j) acc[j][h] = (double4_t){b, b, b, b};
+        for (int j = 0; j < N; ++j) acc[j][h] = (typename Pr::Acc){b, b, b, b};
 #pragma unroll
         for (int q = 0; q < kQuarters; ++q) accq[q][h] = b;
     }
-    double bv[4][NH];
+    T bv[4][NH];
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int h = 0; h < NH; ++h) bv[s][h] = wp[s * COUT + 16 * h];
+        for (int h = 0; h < NH; ++h) bv[s][h] = wp[s * WS + 16 * h];
 #pragma unroll 1
     for (int ty = 0; ty < 3; ++ty) {
         auto row_of = [&](const TileSite &t) { return t.org + (ty == 0 ? t.up : (ty == 2 ? t.dn : 0)); };
@@ -150,47 +191,62 @@ __device__ __forceinline__ void conv_tiles(const unsigned char *fr, int SB, bool
 #pragma unroll
             for (int cb = 0; cb < NCB; ++cb) {
                 // (the last block fetches block 0's again, unused)
-                const double *wn = wp + (tx * NCB + cb + 1) * 16 * COUT;
+                const T *wn = wp + (tx * NCB + cb + 1) * 16 * COUT;
                 if (tx == 2 && cb == NCB - 1 && ty == 2) wn = wp;
-                double bn[4][NH];
+                T bn[4][NH];
 #pragma unroll
                 for (int s = 0; s < 4; ++s)
 #pragma unroll
-                    for (int h = 0; h < NH; ++h) bn[s][h] = wn[s * COUT + 16 * h];
-                auto read = [&](int rw, const TileSite &t, double2 &u, double2 &v) {
+                    for (int h = 0; h < NH; ++h) bn[s][h] = wn[s * WS + 16 * h];
+                // this lane's four channels of a site's K-block
+                auto read = [&](int rw, const TileSite &t, Chunk &u, Chunk &v) {
                     const unsigned char *p = fr + (rw + (tx == 0 ? t.lf : (tx == 2 ? t.rt : 0)));
-                    u = *(const double2 *)(p + cb * 8 * SB);
-                    v = *(const double2 *)(p + (cb * 8 + 1) * SB);
+                    u = *(const Chunk *)(p + cb * (16 / Pr::VEC) * SB);
+                    if constexpr (Pr::VEC == 2) v = *(const Chunk *)(p + (cb * 8 + 1) * SB);
                 };
-                double2 u, v;
+                auto unpack = [](const Chunk &u, const Chunk &v, T (&av)[4]) {
+                    av[0] = u.x;
+                    av[1] = u.y;
+                    if constexpr (Pr::VEC == 2) {
+                        av[2] = v.x;
+                        av[3] = v.y;
+                    } else {
+                        av[2] = u.z;
+                        av[3] = u.w;
+                    }
+                };
+                Chunk u, v;
                 read(row[0], st[0], u, v);
 #pragma unroll
                 for (int j = 0; j < N; ++j) {
-                    double2 un = u, vn = v;
+                    Chunk un = u, vn = v;
                     if (j + 1 < N) read(row[j + 1], st[j + 1], un, vn);
-                    const double av[4] = {u.x, u.y, v.x, v.y};
+                    T av[4];
+                    unpack(u, v, av);
                     if (j + 1 < N || last)
 #pragma unroll
                         for (int s = 0; s < 4; ++s)
 #pragma unroll
                             for (int h = 0; h < NH; ++h)
-                                acc[j][h] = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                                    av[s], bv[s][h], acc[j][h], 0, 0, 0);
+                                acc[j][h] = Pr::mfma(av[s], bv[s][h], acc[j][h]);
                     u = un;
                     v = vn;
                 }
+                if constexpr (Pr::KQ > 0) {
 #pragma unroll
-                for (int q = 0; q < kQuarters; ++q)
-                    if (q < nq) {
-                        read(rowq[q], sq[q], u, v);
-                        const double av[4] = {u.x, u.y, v.x, v.y};
+                    for (int q = 0; q < kQuarters; ++q)
+                        if (q < nq) {
+                            read(rowq[q], sq[q], u, v);
+                            T av[4];
+                            unpack(u, v, av);
 #pragma unroll
-                        for (int s = 0; s < 4; ++s)
+                            for (int s = 0; s < 4; ++s)
 #pragma unroll
-                            for (int h = 0; h < NH; ++h)
-                                accq[q][h] = __builtin_amdgcn_mfma_f64_4x4x4f64(
-                                    av[s], bv[s][h], accq[q][h], 0, 0, 0);
-                    }
+                                for (int h = 0; h < NH; ++h)
+                                    accq[q][h] = __builtin_amdgcn_mfma_f64_4x4x4f64(
+                                        av[s], bv[s][h], accq[q][h], 0, 0, 0);
+                        }
+                }
 #pragma unroll
                 for (int s = 0; s < 4; ++s)
 #pragma unroll
@@ -223,7 +279,7 @@ struct Region {
 // the per-site terms of its configuration live in LDS.  Each proposal whose
 // two spins differ is evaluated in full (the layers in between are not kept),
 // accepted when u < exp(2 dlog), and the terms then replace the chain's.
-template <int C, int NET, int W, int PK, int NMAX, int MODE, int EU>
+template <typename T, int C, int NET, int W, int PK, int NMAX, int MODE, int EU>
 __global__ void __launch_bounds__(W * PK * 64, EU)
 k_frame64(FrameArgs a)
 {
@@ -238,7 +294,9 @@ k_frame64(FrameArgs a)
             __syncthreads();
         }
     };
-    constexpr int CHK = C / 2;                       // 16-byte chunks per site
+    using Pr = Prec<T>;
+    using Chunk = typename Pr::Chunk;
+    constexpr int CHK = C / Pr::VEC;                 // 16-byte chunks per site
     constexpr int NHB = NET == kNetCnn1 ? 1 : C / 16;   // waves per tile (one column block each)
     constexpr int G = W / NHB;                       // tile groups
     static_assert(G >= 1 && G * NHB == W, "waves split into column blocks and tile groups");
@@ -378,6 +436,7 @@ k_frame64(FrameArgs a)
             sf[e] = CHAIN ? cs[q] : a.spins[(int64_t)s * N + q];
         }
         sync();
+        const T *w1 = (const T *)a.w1;
         // first layer from the spins: CNN2's embedding (R_2: the whole array)
         if constexpr (NET == kNetCnn2) {
             const int co = tid % C;
@@ -385,40 +444,40 @@ k_frame64(FrameArgs a)
                 int fx, fy;
                 halo(e, fx, fy);
                 const int8_t sv = sf[e];
-                *(double *)(fr + (co >> 1) * SB + (fy * P + fx) * 16 + (co & 1) * 8) =
-                    a.w1[(sv == 0 ? 0 : (sv > 0 ? 1 : 2)) * C + co];
+                *(T *)(fr + Pr::plane(co) * SB + (fy * P + fx) * 16 + Pr::place(co)) =
+                    w1[(sv == 0 ? 0 : (sv > 0 ? 1 : 2)) * C + co];
             }
         } else {
             // ln cosh (bias, then the taps), or CNN1's convolution and
             // channel-pair max, on R_1
             const uint32_t mul = ((1u << 20) + r1.w - 1) / r1.w;
             const int co = tid % C;
-            double wz0[9], wz1[9], b0, b1 = 0.0;
+            T wz0[9], wz1[9], b0, b1 = 0;
             if constexpr (NET == kNetLnCosh) {
 #pragma unroll
-                for (int t = 0; t < 9; ++t) wz0[t] = a.w1[t * C + co];
-                b0 = a.w1[9 * C + co];
+                for (int t = 0; t < 9; ++t) wz0[t] = w1[t * C + co];
+                b0 = w1[9 * C + co];
             } else {
 #pragma unroll
                 for (int t = 0; t < 9; ++t) {
-                    wz0[t] = a.w1[(2 * co) * 9 + t];
-                    wz1[t] = a.w1[(2 * co + 1) * 9 + t];
+                    wz0[t] = w1[(2 * co) * 9 + t];
+                    wz1[t] = w1[(2 * co + 1) * 9 + t];
                 }
-                b0 = a.w1[18 * C + 2 * co];
-                b1 = a.w1[18 * C + 2 * co + 1];
+                b0 = w1[18 * C + 2 * co];
+                b1 = w1[18 * C + 2 * co + 1];
             }
-            unsigned char *frc = fr + (co >> 1) * SB + (co & 1) * 8;
+            unsigned char *frc = fr + Pr::plane(co) * SB + Pr::place(co);
             for (int p = tid / C; p < r1.w * r1.h; p += NT / C) {
                 const int v = (int)(((uint32_t)p * mul) >> 20), x = p - v * r1.w;
                 const int8_t *nb = sf + v * sw + x;
-                double z0 = b0, z1 = b1;
+                T z0 = b0, z1 = b1;
 #pragma unroll
                 for (int t = 0; t < 9; ++t) {
-                    const double sv = (double)nb[t / 3 * sw + t % 3];
+                    const T sv = (T)nb[t / 3 * sw + t % 3];
                     z0 = fma(wz0[t], sv, z0);
                     if constexpr (NET == kNetCnn1) z1 = fma(wz1[t], sv, z1);
                 }
-                *(double *)(frc + (inside(r1.y0 + v) * P + inside(r1.x0 + x)) * 16) =
+                *(T *)(frc + (inside(r1.y0 + v) * P + inside(r1.x0 + x)) * 16) =
                     NET == kNetCnn1 ? ((z1 > z0) ? z1 : z0) : ln_cosh_fwd(z0);
             }
         }
@@ -429,7 +488,7 @@ k_frame64(FrameArgs a)
             constexpr int XP = NT / CHK;             // sites per stretch
             const Region in = region(l), out = region(l + 2);
             if (in.w == out.w && in.h == out.h) return;
-            const double *src = a.cache + ((int64_t)(l - 1) * a.cB + (s - a.b0)) * N * C;
+            const T *src = (const T *)a.cache + ((int64_t)(l - 1) * a.cB + (s - a.b0)) * N * C;
             const int c = tid % CHK;
             for (int xb = 0; xb < out.w; xb += XP) {
                 const int x = xb + tid / CHK;
@@ -437,7 +496,7 @@ k_frame64(FrameArgs a)
                 const int dx = fx - in.x0 + (fx < in.x0 ? P : 0);
                 const bool side = x < out.w && dx >= in.w, live = x < out.w;
                 const int lx = torus ? fx : wrap1(ax - F + fx, L);
-                const double *gx = src + lx * C + 2 * c;
+                const T *gx = src + lx * C + Pr::VEC * c;
                 unsigned char *fc = fr + c * SB + fx * 16;
                 // row v of the stretch: frame row, and whether this lane copies
                 auto row = [&](int v, bool &on) {
@@ -448,25 +507,25 @@ k_frame64(FrameArgs a)
                 };
                 auto get = [&](int fy, bool on) {
                     const int ly = torus ? fy : wrap1(ay - F + fy, L);
-                    return *(const double2 *)(gx + (on ? ly * L * C : 0));
+                    return *(const Chunk *)(gx + (on ? ly * L * C : 0));
                 };
                 for (int v = 0; v < out.h; v += 4) {
                     bool o0, o1, o2, o3;
                     const int f0 = row(v, o0), f1 = row(v + 1, o1), f2 = row(v + 2, o2), f3 = row(v + 3, o3);
                     if (__ballot(o0 || o1 || o2 || o3) == 0) continue;
-                    const double2 d0 = get(f0, o0), d1 = get(f1, o1), d2 = get(f2, o2), d3 = get(f3, o3);
-                    if (o0) *(double2 *)(fc + f0 * P * 16) = d0;
-                    if (o1) *(double2 *)(fc + f1 * P * 16) = d1;
-                    if (o2) *(double2 *)(fc + f2 * P * 16) = d2;
-                    if (o3) *(double2 *)(fc + f3 * P * 16) = d3;
+                    const Chunk d0 = get(f0, o0), d1 = get(f1, o1), d2 = get(f2, o2), d3 = get(f3, o3);
+                    if (o0) *(Chunk *)(fc + f0 * P * 16) = d0;
+                    if (o1) *(Chunk *)(fc + f1 * P * 16) = d1;
+                    if (o2) *(Chunk *)(fc + f2 * P * 16) = d2;
+                    if (o3) *(Chunk *)(fc + f3 * P * 16) = d3;
                 }
             }
         };
         // base pass: the frame (the whole torus) becomes cache slot l - 1
         auto keep = [&](int l) {
-            double *dst = a.cache + ((int64_t)(l - 1) * a.cB + (s - a.b0)) * N * C;
+            T *dst = (T *)a.cache + ((int64_t)(l - 1) * a.cB + (s - a.b0)) * N * C;
             for (int q = tid; q < N * CHK; q += NT)
-                *(double2 *)(dst + 2 * q) = *(const double2 *)(fr + (q % CHK) * SB + (q / CHK) * 16);
+                *(Chunk *)(dst + Pr::VEC * q) = *(const Chunk *)(fr + (q % CHK) * SB + (q / CHK) * 16);
         };
         if constexpr (NET != kNetCnn2)
             if (part && S > 1) ring(1);
@@ -476,17 +535,17 @@ k_frame64(FrameArgs a)
             if constexpr (BASE)
                 if (a.cache && l - 1 >= 1) keep(l - 1);
             const bool pairs = NET == kNetCnn1 && (l & 1);   // CNN1 convolution 16 -> 32
-            const double *wl, *bias;
+            const T *wl, *bias;
             if constexpr (NET == kNetLnCosh) {
-                wl = a.w + (int64_t)(l - 2) * (9 * C * C + C);
+                wl = (const T *)a.w + (int64_t)(l - 2) * (9 * C * C + C);
                 bias = wl + 9 * C * C;
             } else if constexpr (NET == kNetCnn1) {
                 const int k = (l - 1) >> 1;
-                wl = k == 0 ? a.w : a.w + kC1First + (int64_t)(k - 1) * kC1Block;
+                wl = k == 0 ? (const T *)a.w : (const T *)a.w + kC1First + (int64_t)(k - 1) * kC1Block;
                 if (k > 0 && !pairs) wl += kC1Conv + 32;
                 bias = wl + (pairs ? kC1Conv : kC1ConvT);
             } else {
-                wl = a.w + (int64_t)((l - 1) >> 1) * (36 * C * C + 2 * C) + ((l & 1) ? 0 : 9 * C * C + C);
+                wl = (const T *)a.w + (int64_t)((l - 1) >> 1) * (36 * C * C + 2 * C) + ((l & 1) ? 0 : 9 * C * C + C);
                 bias = wl + 9 * C * C;
             }
             const Region r = region(l);
@@ -497,7 +556,7 @@ k_frame64(FrameArgs a)
             // sites past the full tiles are quarter tiles of the first group
             // with fewer tiles, or a full tile if there are more than 8
             int TF = nl >> 4, NQ = ((nl & 15) + 3) >> 2;
-            if (TF == 0 || NQ > kQuarters) ++TF, NQ = 0;
+            if (TF == 0 || NQ > Pr::KQ) ++TF, NQ = 0;
             const int nq = grp == TF % G ? NQ : 0;
             auto site = [&](int q) {
                 TileSite t;
@@ -505,7 +564,7 @@ k_frame64(FrameArgs a)
                 const int v = (int)(((uint32_t)p * mul) >> 20);
                 const int fx = inside(r.x0 + p - v * r.w), fy = inside(r.y0 + v);
                 const int f = fy * P + fx;
-                t.org = f * 16 + 2 * kq * SB;
+                t.org = f * 16 + (Pr::VEC == 2 ? 2 : 1) * kq * SB;
                 t.to = (q < nl ? f : P * P) * 16;   // past the end: the planes' spare chunk
                 t.up = (fy == 0 ? P - 1 : -1) * P * 16;
                 t.dn = (fy == P - 1 ? 1 - P : 1) * P * 16;
@@ -521,10 +580,10 @@ k_frame64(FrameArgs a)
                 for (int j = 0; j < TN; ++j) st[j] = site((grp + G * j) * 16 + m16);
 #pragma unroll
                 for (int q = 0; q < kQuarters; ++q) sq[q] = site(TF * 16 + 4 * q + (lane & 3));
-                double4_t acc[TN][NH];
-                double accq[kQuarters][NH];
-                conv_tiles<TN, C, C * NH, NH>(fr, SB, last, nq, st, sq,
-                                              wl + 4 * kq * C * NH + 16 * hb + m16,
+                typename Pr::Acc acc[TN][NH];
+                T accq[kQuarters][NH];
+                conv_tiles<T, TN, C, C * NH, NH>(fr, SB, last, nq, st, sq,
+                                              wl + Pr::LANE_CH * kq * C * NH + 16 * hb + m16,
                                               bias + 16 * hb + m16, acc, accq);
                 const bool c2max = NET == kNetCnn2 && (l & 1);
                 if constexpr (NET == kNetLnCosh) {
@@ -554,10 +613,10 @@ k_frame64(FrameArgs a)
                 }
                 sync();                      // every read of the frame for layer l is done
                 const int ch = 16 * hb + m16;
-                unsigned char *frc = fr + (ch >> 1) * SB + (ch & 1) * 8;
+                unsigned char *frc = fr + Pr::plane(ch) * SB + Pr::place(ch);
                 // one result of this lane's column: position p, row `row` of a tile
-                auto store = [&](int p, int to, int row, const double (&zs)[NH]) {
-                    double z = zs[0];
+                auto store = [&](int p, int to, int row, const T (&zs)[NH]) {
+                    T z = zs[0];
                     if constexpr (NH == 2) {
                         z = (zs[1] > z) ? zs[1] : z;
                     } else if constexpr (NET == kNetCnn2) {
@@ -568,17 +627,17 @@ k_frame64(FrameArgs a)
                             z = (z1 > z) ? z1 : z;
                         }
                     }
-                    *(double *)(frc + __shfl(to, row, 64)) = z;
+                    *(T *)(frc + __shfl(to, row, 64)) = z;
                 };
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
                     if (j + 1 < TN || last)
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
-                            double zs[NH];
+                            T zs[NH];
 #pragma unroll
                             for (int h = 0; h < NH; ++h) zs[h] = acc[j][h][i];
-                            store((grp + G * j) * 16 + kq + 4 * i, st[j].to, kq + 4 * i, zs);
+                            store((grp + G * j) * 16 + Pr::row(kq, i), st[j].to, Pr::row(kq, i), zs);
                         }
 #pragma unroll
                 for (int q = 0; q < kQuarters; ++q)
@@ -648,12 +707,22 @@ k_frame64(FrameArgs a)
                 const int fx = inside(r.x0 + p - v * r.w), fy = inside(r.y0 + v);
                 const unsigned char *q = fr + (fy * P + fx) * 16;
                 if constexpr (NET == kNetLnCosh) {
-                    double hs = 0.0;
+                    double hs = 0.0;           // the channels in order
 #pragma unroll
-                    for (int c = 0; c < CHK; ++c) {
-                        const double2 h = *(const double2 *)(q + c * SB);
-                        hs += h.x;
-                        hs += h.y;
+                    for (int c0 = 0; c0 < C; c0 += 16) {
+                        Chunk h[16 / Pr::VEC];
+#pragma unroll
+                        for (int c = 0; c < 16 / Pr::VEC; ++c)
+                            h[c] = *(const Chunk *)(q + (c0 / Pr::VEC + c) * SB);
+#pragma unroll
+                        for (int c = 0; c < 16; ++c) {
+                            if constexpr (Pr::VEC == 2) {
+                                hs += c & 1 ? h[c >> 1].y : h[c >> 1].x;
+                            } else {
+                                const Chunk &k = h[c & 3];
+                                hs += (double)(c >> 2 == 0 ? k.x : (c >> 2 == 1 ? k.y : (c >> 2 == 2 ? k.z : k.w)));
+                            }
+                        }
                     }
                     take(site_of(fx, fy), hs, 0);
                 } else {
@@ -726,7 +795,7 @@ k_frame64(FrameArgs a)
 
 inline size_t frame_lds(const nqs_ctx *c, int P, bool chains = false)
 {
-    size_t n = (size_t)(c->C / 2) * plane_bytes16(P) + (size_t)(((P + 2) * (P + 2) + 15) & ~15);
+    size_t n = (size_t)(c->C / (c->dtype == NQS_FP32 ? 4 : 2)) * plane_bytes16(P) + (size_t)(((P + 2) * (P + 2) + 15) & ~15);
     if (c->net == kNetCnn2) n += sizeof(double) * ((c->C == 32 ? 2 * (size_t)P * P : 0) + 9 * c->C + 1);
     if (chains) n += (size_t)c->N * (2 * sizeof(double) + 1);
     return (n + 15) & ~(size_t)15;
@@ -740,10 +809,10 @@ inline int frame_reach(const nqs_ctx *c)
     return c->net == kNetLnCosh ? c->K : (c->net == kNetCnn1 ? 2 * c->K : 2 * c->K + 1);
 }
 
-template <int C, int NET, int W, int PK, int NMAX, int MODE, int EU>
+template <typename T, int C, int NET, int W, int PK, int NMAX, int MODE, int EU>
 void launch_w(const nqs_ctx *c, FrameArgs a, int64_t items, hipStream_t s)
 {
-    const auto kernel = k_frame64<C, NET, W, PK, NMAX, MODE, EU>;
+    const auto kernel = k_frame64<T, C, NET, W, PK, NMAX, MODE, EU>;
     a.lds = (int)frame_lds(c, a.P, MODE == kChains);
     const int lds = a.lds * PK;
     (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -764,38 +833,40 @@ struct FrameShape {
 constexpr FrameShape kShapes16[4] = {{1, 4, 7}, {1, 4, 10}, {4, 1, 5}, {8, 1, 10}};
 constexpr FrameShape kShapes32[3] = {{4, 1, 5}, {4, 1, 8}, {8, 1, 10}};
 
-template <int C, int NET, int MODE>
+template <typename T, int C, int NET, int MODE>
 void launch_m(const nqs_ctx *c, const FrameArgs &a, int64_t items, int shape, hipStream_t s)
 {
     if constexpr (C == 16) {
         constexpr int EU = NET == kNetCnn1 ? 2 : 3;
-        if (shape == 0) return launch_w<C, NET, 1, 4, 7, MODE, EU>(c, a, items, s);
+        if (shape == 0) return launch_w<T, C, NET, 1, 4, 7, MODE, EU>(c, a, items, s);
         if constexpr (NET != kNetCnn1 && MODE == kItems)
-            if (shape == 1) return launch_w<C, NET, 1, 4, 10, MODE, 2>(c, a, items, s);
-        if (shape == 2) return launch_w<C, NET, 4, 1, 5, MODE, EU>(c, a, items, s);
+            if (shape == 1) return launch_w<T, C, NET, 1, 4, 10, MODE, 2>(c, a, items, s);
+        if (shape == 2) return launch_w<T, C, NET, 4, 1, 5, MODE, EU>(c, a, items, s);
     } else {
-        if (shape == 0) return launch_w<C, NET, 4, 1, 5, MODE, 3>(c, a, items, s);
+        if (shape == 0) return launch_w<T, C, NET, 4, 1, 5, MODE, 3>(c, a, items, s);
         if constexpr (MODE == kItems)
-            if (shape == 1) return launch_w<C, NET, 4, 1, 8, MODE, 2>(c, a, items, s);
+            if (shape == 1) return launch_w<T, C, NET, 4, 1, 8, MODE, 2>(c, a, items, s);
     }
-    launch_w<C, NET, 8, 1, 10, MODE, 2>(c, a, items, s);
+    launch_w<T, C, NET, 8, 1, 10, MODE, 2>(c, a, items, s);
 }
 
-template <int C, int NET>
+template <typename T, int C, int NET>
 void launch_c(const nqs_ctx *c, const FrameArgs &a, int mode, int64_t items, int shape,
               hipStream_t s)
 {
     if (mode == kBase)
-        launch_w<C, NET, 8, 1, 10, kBase, 2>(c, a, items, s);
+        launch_w<T, C, NET, 8, 1, 10, kBase, 2>(c, a, items, s);
     else if (mode == kChains)
-        launch_m<C, NET, kChains>(c, a, items, shape, s);
+        launch_m<T, C, NET, kChains>(c, a, items, shape, s);
     else
-        launch_m<C, NET, kItems>(c, a, items, shape, s);
+        launch_m<T, C, NET, kItems>(c, a, items, shape, s);
 }
 
 // one translation unit per network (k_frame64_*.hip)
 void launch_ln16(const nqs_ctx *c, const FrameArgs &a, int mode, int64_t items, int shape, hipStream_t s);
 void launch_ln32(const nqs_ctx *c, const FrameArgs &a, int mode, int64_t items, int shape, hipStream_t s);
+void launch_ln16f(const nqs_ctx *c, const FrameArgs &a, int mode, int64_t items, int shape, hipStream_t s);
+void launch_ln32f(const nqs_ctx *c, const FrameArgs &a, int mode, int64_t items, int shape, hipStream_t s);
 void launch_cnn1(const nqs_ctx *c, const FrameArgs &a, int mode, int64_t items, int shape, hipStream_t s);
 void launch_cnn2_16(const nqs_ctx *c, const FrameArgs &a, int mode, int64_t items, int shape, hipStream_t s);
 void launch_cnn2_32(const nqs_ctx *c, const FrameArgs &a, int mode, int64_t items, int shape, hipStream_t s);

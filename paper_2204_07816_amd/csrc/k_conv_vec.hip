@@ -22,18 +22,8 @@ constexpr int kThreads = 256;
 
 __device__ inline int wrapi(int a, int L) { return a < 0 ? a + L : (a >= L ? a - L : a); }
 
-// ln cosh z: FP64 in the shared branch-free form; FP32 with e = expm1(|z|),
-// cosh|z| - 1 = e^2 / (2 (1 + e)), so ln cosh z = log1p(e^2 / (2 + 2e)) keeps
-// full relative precision at small |z|, and for |z| > 1 the form
-// |z| - ln 2 + log1p(exp(-2|z|)) avoids overflow.
 __device__ inline double ln_cosh(double z) { return ln_cosh_fwd(z); }
-__device__ inline float ln_cosh(float z)
-{
-    const float a = fabsf(z);
-    if (a > 1.0f) return a - 0.693147180559945f + log1pf(expf(-2.0f * a));
-    const float e = expm1f(a);
-    return log1pf(e * e / (2.0f + 2.0f * e));
-}
+__device__ inline float ln_cosh(float z) { return ln_cosh_fwd(z); }
 
 // Spin of site q in the configuration of a plane: the sample's spins, with
 // the pair (qi, qj) exchanged when the plane is an exchanged configuration.

@@ -1,0 +1,12 @@
+#include "frame64.h"
+
+namespace nqs {
+namespace frame {
+
+void launch_ln32f(const nqs_ctx *c, const FrameArgs &a, int mode, int64_t items, int shape, hipStream_t s)
+{
+    launch_c<float, 32, kNetLnCosh>(c, a, mode, items, shape, s);
+}
+
+}  // namespace frame
+}  // namespace nqs

@@ -15,6 +15,8 @@ void launch_any(const nqs_ctx *c, const FrameArgs &a, int mode, int64_t items, i
         launch_cnn1(c, a, mode, items, shape, s);
     else if (c->net == kNetCnn2)
         (c->C == 32 ? launch_cnn2_32 : launch_cnn2_16)(c, a, mode, items, shape, s);
+    else if (c->dtype == NQS_FP32)
+        (c->C == 32 ? launch_ln32f : launch_ln16f)(c, a, mode, items, shape, s);
     else
         (c->C == 32 ? launch_ln32 : launch_ln16)(c, a, mode, items, shape, s);
 }
@@ -26,7 +28,7 @@ int frame_shape(const nqs_ctx *c, int P, bool regions)
     const int nhb = c->net == kNetCnn1 ? 1 : c->C / 16;
     const int wd = regions ? std::min(c->L, 2 + 2 * (c->net == kNetCnn2 ? 2 * c->K : frame_reach(c)))
                            : c->L;
-    const int T = (wd * wd + 15 - 4 * kQuarters) / 16;
+    const int T = (wd * wd + 15 - (c->dtype == NQS_FP32 ? 0 : 4 * kQuarters)) / 16;
     const FrameShape *sh = c->C == 16 ? kShapes16 : kShapes32;
     const int ns = c->C == 16 ? 4 : 3;
     for (int i = 0; i < ns - 1; ++i) {
@@ -44,7 +46,10 @@ FrameArgs frame_args(const nqs_ctx *c, const int8_t *spins)
     FrameArgs a{};
     a.spins = spins;
     const int C = c->C;
-    if (c->net == kNetLnCosh) {
+    if (c->dtype == NQS_FP32) {
+        a.w1 = c->w_vec32;
+        a.w = c->w_vec32 + 10 * C;
+    } else if (c->net == kNetLnCosh) {
         a.w1 = c->w_vec64;
         a.w = c->w_vec64 + 10 * C;
     } else if (c->net == kNetCnn1) {
@@ -65,7 +70,7 @@ FrameArgs frame_args(const nqs_ctx *c, const int8_t *spins)
 
 bool frame64_ok(const nqs_ctx *c)
 {
-    if (c->dtype != NQS_FP64) return false;
+    if (c->dtype != NQS_FP64 && c->dtype != NQS_FP32) return false;
     if (c->net == kNetCnn1 ? c->C != 16 : (c->C != 16 && c->C != 32)) return false;
     if (c->net == kNetLnCosh && c->K < 2) return false;
     return frame_lds(c, c->L) <= kLdsMax;
@@ -89,7 +94,7 @@ int64_t frame64_slots(const nqs_ctx *c)
 
 size_t frame64_cache_bytes(const nqs_ctx *c, int64_t cB)
 {
-    return sizeof(double) * (size_t)frame64_slots(c) * (size_t)cB * c->N * c->C;
+    return (c->dtype == NQS_FP32 ? sizeof(float) : sizeof(double)) * (size_t)frame64_slots(c) * (size_t)cB * c->N * c->C;
 }
 
 // samples per cache fill: at most 16 GiB of cached activations
@@ -100,7 +105,7 @@ int64_t cone64_chunk(const nqs_ctx *c, int64_t B)
 }
 
 void frame64_base(const nqs_ctx *c, const int8_t *spins, int64_t cB, int64_t b0, int64_t nb,
-                  double *cache, double *site, int32_t *neg, double *f, int8_t *sgn, hipStream_t s)
+                  void *cache, double *site, int32_t *neg, double *f, int8_t *sgn, hipStream_t s)
 {
     if (nb <= 0) return;
     FrameArgs a = frame_args(c, spins);
@@ -118,7 +123,7 @@ void frame64_base(const nqs_ctx *c, const int8_t *spins, int64_t cB, int64_t b0,
 
 void frame64_conn(const nqs_ctx *c, const int8_t *spins, const uint32_t *queue,
                   const int64_t *offsets, int64_t cap, int64_t cB, int64_t b0, int64_t nb,
-                  const double *cache, const double *site, const int32_t *neg, double *dlog,
+                  const void *cache, const double *site, const int32_t *neg, double *dlog,
                   int8_t *isign, hipStream_t s)
 {
     if (nb <= 0 || cap <= 0) return;
@@ -126,7 +131,7 @@ void frame64_conn(const nqs_ctx *c, const int8_t *spins, const uint32_t *queue,
     a.queue = queue;
     a.offsets = offsets;
     a.cap = cap;
-    a.cache = const_cast<double *>(cache);
+    a.cache = const_cast<void *>(cache);
     a.site = const_cast<double *>(site);
     a.neg = const_cast<int32_t *>(neg);
     a.cB = cB;
@@ -164,7 +169,7 @@ void frame64_chains(const nqs_ctx *c, int8_t *spins, int64_t B, int n_steps, con
     // of 16, 32 steps of 512 chains: 0.65 ms against 1.17 for one wave and 0.82
     // for eight) while their tiles allow; one wave each where the chains alone
     // fill three waves per SIMD (4096 chains: 3.25 against 3.54 ms).
-    const int T = (c->N + 15 - 4 * kQuarters) / 16;
+    const int T = (c->N + 15 - (c->dtype == NQS_FP32 ? 0 : 4 * kQuarters)) / 16;
     int shape = 3;
     if (c->C == 16 && T <= kShapes16[0].NMAX && B >= 12 * (int64_t)c->n_cu)
         shape = 0;

@@ -5,7 +5,7 @@ namespace frame {
 
 void launch_cnn2_32(const nqs_ctx *c, const FrameArgs &a, int mode, int64_t items, int shape, hipStream_t s)
 {
-    launch_c<32, kNetCnn2>(c, a, mode, items, shape, s);
+    launch_c<double, 32, kNetCnn2>(c, a, mode, items, shape, s);
 }
 
 }  // namespace frame

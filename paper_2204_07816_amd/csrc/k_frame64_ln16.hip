@@ -5,7 +5,7 @@ namespace frame {
 
 void launch_ln16(const nqs_ctx *c, const FrameArgs &a, int mode, int64_t items, int shape, hipStream_t s)
 {
-    launch_c<16, kNetLnCosh>(c, a, mode, items, shape, s);
+    launch_c<double, 16, kNetLnCosh>(c, a, mode, items, shape, s);
 }
 
 }  // namespace frame

@@ -384,7 +384,7 @@ nqs_status frame_ratio_stage(nqs_ctx *c, const int8_t *spins, int B, bool region
     Workspace &w = c->ws;
     NQS_TRY(frame_reserve(c, B, cap, regions, s));
     const int64_t chunk = regions ? frame_chunk(c, B) : B;
-    double *cache = regions ? (double *)w.cache.ptr : nullptr;
+    void *cache = regions ? w.cache.ptr : nullptr;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (c->timing) {
         (void)hipEventCreate(&e0);

@@ -129,6 +129,26 @@ __device__ inline double ln_cosh_fwd(double z)
     return ln_cosh_of(a, expm1_m2(a));
 }
 
+// FP32: with e = expm1(|z|), cosh|z| - 1 = e^2 / (2 (1 + e)), so ln cosh z =
+// log1p(e^2 / (2 + 2e)) keeps full relative precision at small |z|, and for
+// |z| > 1 the form |z| - ln 2 + log1p(exp(-2|z|)) avoids overflow.  The lanes
+// of a wave usually fall on both sides, so the logarithm is taken once, after
+// the branch (energies at 10x10, 4 layers of 16, 1024 samples: 5.33 -> 5.00 ms).
+__device__ inline float ln_cosh_fwd(float z)
+{
+    const float a = fabsf(z);
+    const bool far = a > 1.0f;
+    float t;
+    if (far) {
+        t = expf(-2.0f * a);
+    } else {
+        const float e = expm1f(a);
+        t = e * e / (2.0f + 2.0f * e);
+    }
+    const float l = log1pf(t);
+    return far ? a - 0.693147180559945f + l : l;
+}
+
 // Hamiltonian of a context: the J1-J2 spin model [Sec. 6.1, Eq. J1J2] or
 // the t-J model [Sec. 6.1, Eq. tJ] (site values +1 / -1 / 0, nearest-
 // neighbour bonds only, J held in J1).
@@ -319,11 +339,11 @@ bool frame64_suits(const nqs_ctx *c);
 int64_t frame64_slots(const nqs_ctx *c);
 size_t frame64_cache_bytes(const nqs_ctx *c, int64_t cB);
 void frame64_base(const nqs_ctx *c, const int8_t *spins, int64_t cB, int64_t b0, int64_t nb,
-                  double *cache, double *site, int32_t *neg, double *f, int8_t *sgn,
+                  void *cache, double *site, int32_t *neg, double *f, int8_t *sgn,
                   hipStream_t s);
 void frame64_conn(const nqs_ctx *c, const int8_t *spins, const uint32_t *queue,
                   const int64_t *offsets, int64_t cap, int64_t cB, int64_t b0, int64_t nb,
-                  const double *cache, const double *site, const int32_t *neg, double *dlog,
+                  const void *cache, const double *site, const int32_t *neg, double *dlog,
                   int8_t *isign, hipStream_t s);
 // n_steps Metropolis steps of B chains, one launch (rnd, un: [n_steps][B])
 bool frame64_chains_ok(const nqs_ctx *c);

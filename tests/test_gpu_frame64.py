@@ -91,3 +91,36 @@ def test_chains_equal_the_oracle(L, K, C, B, steps):
     assert np.array_equal(spd.cpu().numpy(), want)
     assert np.array_equal(got.cpu().numpy(), acc)
     assert ctx.get_error() == 0
+
+
+@pytest.mark.parametrize("dtype", ["fp64", "fp32"])
+@pytest.mark.parametrize("L,K,C,J2", [
+    (4, 2, 16, 0.5), (6, 3, 32, 0.0), (10, 4, 16, 0.5), (12, 5, 32, 0.5), (14, 2, 16, 0.5),
+    (16, 6, 32, 0.5), (18, 4, 16, 0.0), (24, 2, 32, 0.5),
+])
+def test_ratios_equal_the_layered_amplitudes(dtype, L, K, C, J2):
+    """Every neuron of the frame form equals the layered kernels' (log_psi) bit
+    for bit, so a log ratio is the difference of two of their amplitudes but
+    for the order of the FP64 sums over N C terms of size f / (N C): at most
+    log2 of the terms' roundings of f in a tree, 64 for a serial order."""
+    w = inputs.stress_weights(K, C, 1.0, 51)
+    sp = inputs.spins_any(L, 1, 52)
+    ctx = nqs.Context(L, 1.0, J2, K, C, w, dtype)
+    spd = torch.as_tensor(sp).cuda()
+    counts, offs, bonds, _, _ = ctx.connected(spd)
+    n = int(offs[-1])
+    b = bonds[:n].cpu().numpy()
+    dx, dy = np.array([1, 0, 1, 1]), np.array([0, 1, 1, -1])
+    i = b >> 2
+    x, y = i % L, i // L
+    j = (y + dy[b & 3]) % L * L + (x + dx[b & 3]) % L
+    pick = np.arange(n) if n <= 400 else np.linspace(0, n - 1, 400).astype(int)
+    ex = np.repeat(sp.reshape(1, -1), len(pick), 0)
+    r = np.arange(len(pick))
+    ex[r, i[pick]], ex[r, j[pick]] = sp.reshape(-1)[j[pick]], sp.reshape(-1)[i[pick]]
+    f0 = float(ctx.log_psi(spd)[0][0])
+    f1 = ctx.log_psi(torch.as_tensor(ex.reshape(-1, L, L)).cuda())[0].cpu().numpy()
+    bound = 64 * EPS * (abs(f0) + np.abs(f1))
+    for mode in ("full", "auto"):
+        d = ctx.log_ratios(spd, mode=mode)[:n].cpu().numpy()[pick]
+        assert np.all(np.abs(d - (f1 - f0)) <= bound)
