@@ -475,12 +475,6 @@ bool mfma_supported(const nqs_ctx *c)
     return pick_variant(c, true, &v, &lds);
 }
 
-bool mfma_inc_supported(const nqs_ctx *c)
-{
-    // anchor offsets must stay within one period of the torus
-    return mfma_supported(c) && c->L >= c->K + 2 && 2 * mfma_inc_lds_bytes(c) <= 160 * 1024 - 1024;
-}
-
 int mfma_lds_full_ok(const nqs_ctx *c)
 {
     Variant v;
@@ -510,13 +504,17 @@ void mfma_conn_forward_jobs(nqs_mode mode, const ConnJob *jobs, int n, hipStream
 {
     if (n <= 0) return;
     if (mode == NQS_INCREMENTAL) {
-        // lattices the unwrapped-window kernel serves share one launch of it;
-        // the others (wrapped windows, 16 channels) one launch of the general
-        // kernel: each lattice runs exactly as in its single-lattice call
+        // Deep unwrapped windows of 32 channels share one launch of the cone
+        // kernel, where a workgroup's waves share each layer's weights; all else
+        // one launch of the frame kernel, a wave per configuration.  Layers of
+        // up to 7 tiles are too short for the former (20x20, 32 channels: 3
+        // layers 1.69 against 1.15 ms, 4 layers 2.51 against 1.90), from 5
+        // layers on it leads (5: 1.76 against 1.83, 6: 2.31 against 2.68, 36x36
+        // with 8: 3.05 against 5.61).
         ConnJob cone[kMaxConnJobs], rest[kMaxConnJobs];
         int nc = 0, nr = 0;
         for (int i = 0; i < n; ++i) {
-            if (cone_supported(jobs[i].c))
+            if (cone_supported(jobs[i].c) && !(jobs[i].c->K <= 4 && mfma_inc_supported(jobs[i].c)))
                 cone[nc++] = jobs[i];
             else
                 rest[nr++] = jobs[i];

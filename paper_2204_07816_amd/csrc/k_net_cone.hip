@@ -1,10 +1,9 @@
 // k_net_cone.hip -- the exchanged-configuration pass in incremental mode for
 // lattices wide enough that no window of the receptive cone wraps around the
-// torus (L >= 2K + 4) and 32 channels: the form taken by the large lattices
-// the local energy is dominated by [Sec. 5.4.1].
+// torus (L >= 2K + 4) and 32 channels: the form taken, from five layers on, by
+// the large lattices the local energy is dominated by [Sec. 5.4.1].
 //
-// The method is that of the general incremental kernel: an exchange of the
-// antiparallel pair (i, j) changes layer k only on R_k, the bounding
+// An exchange of the antiparallel pair (i, j) changes layer k only on R_k, the bounding
 // rectangle of the sites within Chebyshev distance k of i or j; layer k is
 // recomputed on R_k from window W_k = R_{k+1} (LDS), which holds layer k-1 of
 // this configuration on R_{k-1} and the cached base-pass activations on the

@@ -199,7 +199,6 @@ nqs_status pack_weights(nqs_ctx *c)
                 return st;
             return NQS_OK;
         }
-        if (!c->ring_tab && (st = mfma_build_ring_tables(c)) != NQS_OK) return st;
         if (cone_supported(c) && !c->cone_tab && (st = cone_build_ring_tables(c)) != NQS_OK)
             return st;
     }
@@ -256,9 +255,11 @@ nqs_mode resolve_mode(const nqs_ctx *c, nqs_mode m)
     return (inc < 0.7 * full && mfma_inc_supported(c)) ? NQS_INCREMENTAL : NQS_FULL;
 }
 
-// Where a requested mode leads.  `regions`: FULL reached by AUTO on an FP64
-// network whose planes fit the LDS: the neurons that an exchange can change
-// are recomputed and the others taken from the base pass (the same values).
+// Where a requested mode leads.  `regions`: FULL reached by AUTO where the
+// neurons that an exchange can change may be recomputed and the others taken
+// from the base pass (the same values): FP64 and FP32 networks whose planes fit
+// the LDS, and BF16 networks that the incremental kernels serve, unless their
+// own timing chose FULL.
 struct Form {
     nqs_mode mode;
     bool regions;
@@ -267,7 +268,20 @@ struct Form {
 Form resolve_form(const nqs_ctx *c, nqs_mode m)
 {
     const nqs_mode r = resolve_mode(c, m);
-    return Form{r, m == NQS_AUTO && r == NQS_FULL && frame64_ok(c)};
+    const bool can = c->dtype == NQS_BF16 ? (!c->tuned && incremental_ok(c)) : frame64_ok(c);
+    return Form{r, m == NQS_AUTO && r == NQS_FULL && can};
+}
+
+// The kernel family of a BF16 exchanged pass of at most `cap` configurations.
+// Regions pay even where they cover the torus (10x10, 8 layers of 32 channels,
+// 256 samples: 3.41 -> 1.11 ms; 4x4, 2 layers, 2048 samples: 0.71 -> 0.19 ms),
+// because one wave per configuration needs no barriers.  With few
+// configurations the workgroup per configuration of FULL ends sooner (8x8, 6
+// layers of 16 channels, one sample, at most 256 configurations: 44 us against
+// 55; four samples: 55 either way), so the line lies at four per CU.
+nqs_mode bf16_conn_mode(const nqs_ctx *c, Form f, int64_t cap)
+{
+    return f.regions && cap >= (int64_t)4 * c->n_cu ? NQS_INCREMENTAL : f.mode;
 }
 
 #define NQS_TRY(x)                        \
@@ -497,7 +511,7 @@ nqs_status log_ratio_stage(nqs_ctx *c, const int8_t *spins, int B, Form form,
             (void)hipEventCreate(&e1);
             (void)hipEventRecord(e0, s);
         }
-        mfma_conn_forward(c, mode, spins, (uint32_t *)w.queue.ptr, (int64_t *)w.qlen.ptr, cap,
+        mfma_conn_forward(c, bf16_conn_mode(c, form, cap), spins, (uint32_t *)w.queue.ptr, (int64_t *)w.qlen.ptr, cap,
                           (double *)w.hsum.ptr, w.cache.ptr, dlog, nullptr, s);
         if (c->timing) {
             (void)hipEventRecord(e1, s);
@@ -862,8 +876,6 @@ nqs_status nqs_destroy(nqs_ctx *c)
     free_dev(c->w_mfma);
     free_dev(c->w_mfma_lo);
     free_dev(c->w_l1);
-    free_dev(c->ring_tab);
-    free_dev(c->ring_off);
     free_dev(c->cone_tab);
     free_dev(c->ls_tab);
     free_dev(c->fr_tab);
@@ -1247,8 +1259,9 @@ nqs_status nqs_local_energy_multi(const nqs_eloc_job *jobs, int32_t n, nqs_mode 
         ConnJob cj[kMaxConnJobs];
         int k = 0;
         for (int i = 0; i <= n; ++i) {
-            if (i < n && jobs[i].B > 0 && resolve_mode(jobs[i].ctx, mode) == m) {
-                nqs_ctx *c = jobs[i].ctx;
+            nqs_ctx *c = i < n ? jobs[i].ctx : nullptr;
+            if (c && jobs[i].B > 0 &&
+                bf16_conn_mode(c, resolve_form(c, mode), bonds_per_sample(c) * jobs[i].B) == m) {
                 cj[k++] = ConnJob{c, jobs[i].spins, (const uint32_t *)c->ws.queue.ptr,
                                   (const int64_t *)c->ws.qlen.ptr, bonds_per_sample(c) * jobs[i].B,
                                   (const double *)c->ws.hsum.ptr, c->ws.cache.ptr,

@@ -244,9 +244,7 @@ struct nqs_ctx {
     uint16_t *w_mfma = nullptr;   // BF16 MFMA A-operand packing, layers 2..K
     uint16_t *w_mfma_lo = nullptr;  // BF16X3: the lo parts of the same packing
     float *w_l1 = nullptr;        // layer-1 weights + all biases, FP32, MFMA path
-    int32_t *ring_tab = nullptr;  // incremental mode: ring lists per bond type and layer
-    int32_t *ring_off = nullptr;
-    int32_t *cone_tab = nullptr;  // same, for the unwrapped-window kernel
+    int32_t *cone_tab = nullptr;  // cone kernel: ring lists per bond type and layer
     std::vector<int> cone_off;    // [4][16] entry offsets of cone_tab
     int32_t *ls_tab = nullptr;    // frame ring tables of the lockstep cone kernel
     std::vector<int> ls_off;      // [4][16] entry offsets of ls_tab
@@ -410,12 +408,7 @@ int mfma_lds_full_ok(const nqs_ctx *c);
 // One launch over the exchanged configurations of 1..kMaxConnJobs contexts of
 // one network shape (mode NQS_FULL or NQS_INCREMENTAL, supported by all).
 void mfma_conn_forward_jobs(nqs_mode mode, const ConnJob *jobs, int n, hipStream_t s);
-// incremental-mode kernel (k_net_inc.hip)
-nqs_status mfma_build_ring_tables(nqs_ctx *c);
-size_t mfma_inc_lds_bytes(const nqs_ctx *c);
-void mfma_inc_forward(const nqs_ctx *c, const int8_t *spins, const uint32_t *queue,
-                      const int64_t *qlen, int64_t capacity, const double *hsum,
-                      const void *cache, double *dlog, hipStream_t s);
+// incremental mode where the cone kernel is not taken (k_frame_bf16.hip)
 bool mfma_inc_supported(const nqs_ctx *c);
 // jobs: 1..kMaxConnJobs contexts of one network shape, all mfma_inc_supported
 void mfma_inc_forward_jobs(const ConnJob *jobs, int n, hipStream_t s);
