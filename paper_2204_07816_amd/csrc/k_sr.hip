@@ -8,9 +8,10 @@
 // O is read as FP32 or FP64; every product, sum and dot is FP64.  Scalars
 // (alpha, beta, r.r) stay on the device, so the solve never synchronises
 // with the host and can be captured in a graph.  All reductions are two-stage
-// with a fixed order (deterministic).  One iteration is five launches: Obar p,
-// the partial column sums of Obar^T u, then three kernels that each finish the
-// previous one's reduction themselves (see k_ap_dot).
+// with a fixed order (deterministic), the same for every launch shape.  One
+// iteration is four launches (Obar p, the partial column sums of Obar^T u, Ap
+// with p.Ap, the update of x and r), three where P is small; each finishes the
+// previous one's reduction itself (see k_rowdot).
 #include <algorithm>
 
 #include "nqs_internal.h"
@@ -30,17 +31,24 @@ struct SrCtl {
 __device__ inline double ld(const float *p, int64_t i) { return (double)p[i]; }
 __device__ inline double ld(const double *p, int64_t i) { return p[i]; }
 
-__device__ double block_sum(double v, double *sh)
+// Sum over the block's kThreads values, the binary tree of offsets 128 .. 1, in
+// every thread.  One barrier, and every wave sums for itself.
+__device__ __forceinline__ double tree_sum(const double *sh)
+{
+    static_assert(kThreads == 256, "four waves");
+    const int l = threadIdx.x & 63;
+    double v = (sh[l] + sh[l + 128]) + (sh[l + 64] + sh[l + 192]);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+    return __shfl(v, 0, 64);
+}
+
+// sh: kThreads values, used by no call before the next barrier
+__device__ __forceinline__ double block_sum(double v, double *sh)
 {
     sh[threadIdx.x] = v;
     __syncthreads();
-    for (int off = kThreads / 2; off > 0; off >>= 1) {
-        if (threadIdx.x < off) sh[threadIdx.x] += sh[threadIdx.x + off];
-        __syncthreads();
-    }
-    const double r = sh[0];
-    __syncthreads();
-    return r;
+    return tree_sum(sh);
 }
 
 // 16-byte vectors of O: VW consecutive elements (4 FP32 or 2 FP64)
@@ -65,16 +73,19 @@ template <typename OT> struct Vec<OT, 1> {
 };
 
 // part[c][p] = sum_{s in chunk c} (O[s][p] - sub[p]) * wt[s]   (sub / wt may be null)
-// Each thread owns VW consecutive columns (one 16-byte load per row when
-// P is a multiple of VW); every column still sums its rows in order.
+// A wave owns 64 VW consecutive columns of one chunk (VW elements a lane, 16
+// bytes where that leaves waves for the whole chip) and keeps 16 rows of loads
+// in flight; every column sums its rows in order whatever VW is.  In blocks of
+// four waves, a load or two in flight, 512 rows of 28,064 floats took 21 us, now
+// 9.7; 2048 rows of 46,560 are bound by HBM, 64 us before and now (6 TB/s).
 template <typename OT, int VW>
-__global__ void __launch_bounds__(kThreads)
+__global__ void __launch_bounds__(64)
 k_colsum(const OT *__restrict__ O, int64_t B, int64_t P, const double *__restrict__ sub,
          const double *__restrict__ wt, int64_t rows_per_chunk, double *__restrict__ part,
          const SrCtl *ctl)
 {
     if (ctl && ctl->done) return;
-    const int64_t p = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * VW;
+    const int64_t p = ((int64_t)blockIdx.x * 64 + threadIdx.x) * VW;
     if (p >= P) return;
     const int64_t s0 = (int64_t)blockIdx.y * rows_per_chunk;
     const int64_t s1 = min(B, s0 + rows_per_chunk);
@@ -84,6 +95,7 @@ k_colsum(const OT *__restrict__ O, int64_t B, int64_t P, const double *__restric
         m[q] = sub ? sub[p + q] : 0.0;
         acc[q] = 0.0;
     }
+#pragma unroll 16
     for (int64_t s = s0; s < s1; ++s) {
         double o[VW];
         Vec<OT, VW>::get(O + s * P + p, o);
@@ -108,51 +120,122 @@ __global__ void k_colsum_final(const double *__restrict__ part, int nchunk, int6
     out[p] = acc * scale + (v ? lam * v[p] : 0.0);
 }
 
-// u[s] = sum_p (O[s][p] - obar[p]) v[p]: kRows rows per block, each thread
-// taking VW consecutive elements per step (16-byte loads of O); the FP64
-// vectors obar and v are read once per step for all the block's rows.  Each
-// row's sum has the same order whatever the number of rows per block.
-constexpr int kRows = 4;
+// The sum of n <= any block partials, in every thread (the same in every block).
+__device__ double sum_parts(const double *part, int n, double *sh)
+{
+    double acc = 0.0;
+    for (int i = threadIdx.x; i < n; i += kThreads) acc += part[i];
+    return block_sum(acc, sh);
+}
 
-template <typename OT, int VW>
+// State of the recursion that the launches of an iteration share.
+struct Cg {
+    double *x, *r, *p, *ap;
+    double *pap_part, *rr_part;   // [nblk] partials of p.Ap and r.r
+    int64_t P;
+    int nblk, it;
+    SrCtl *ctl;
+};
+
+// beta of iteration g.it > 0 from the previous one's partials of r.r.  r.r of
+// the state before iteration i lives in slot i & 1, so a recording block can
+// write the new one while the others still read the old one.
+__device__ __forceinline__ double beta_of(const Cg &g, double *sh, double &rr)
+{
+    rr = sum_parts(g.rr_part, g.nblk, sh);
+    return rr / g.ctl->rrv[(g.it - 1) & 1];
+}
+
+// Records r.r after g.it iterations: ||r|| <= 1e-30 ||F|| is converged far
+// beyond FP64 resolution.
+__device__ __forceinline__ void record(const Cg &g, double rr, double beta)
+{
+    g.ctl->rrv[g.it & 1] = rr;
+    g.ctl->rr = rr;
+    g.ctl->beta = beta;
+    g.ctl->it = g.it;
+    if (!(rr > g.ctl->ff * 1e-60)) g.ctl->done = 1;
+}
+
+// First launch of an iteration: u[s] = sum_p (O[s][p] - obar[p]) v[p].  FLY:
+// v = r + beta p is formed here element by element (k_ap_small writes it back),
+// which saves a launch of 3 to 5 us but reads a third vector per row; else
+// v = p.  kRows rows per block, each thread taking VW consecutive elements per
+// step (16-byte loads of O); the FP64 vectors are read once per step for all
+// the block's rows.  One or two rows are loaded together (a row past the end
+// repeats the last); four one after the other, since their loads in one burst
+// push the vectors out of the first-level cache (2048 rows of 46,560 floats:
+// 75 us against 66, which is 5.8 TB/s).  Each row's sum has the same order
+// whatever kRows is.
+template <typename OT, int VW, int kRows, bool FLY>
 __global__ void __launch_bounds__(kThreads)
-k_rowdot(const OT *__restrict__ O, int64_t nrows, int64_t P, const double *__restrict__ obar,
-         const double *__restrict__ v, double *__restrict__ u, const SrCtl *ctl)
+k_rowdot(const OT *__restrict__ O, int64_t nrows, const double *__restrict__ obar, Cg g,
+         double *__restrict__ u)
 {
     __shared__ double sh[kRows][kThreads];
-    if (ctl->done) return;
+    __shared__ double shb[kThreads];
+    if (g.ctl->done) return;
+    const int64_t P = g.P;
+    double b = 0.0;
+    if (FLY) {
+        double rr;
+        b = beta_of(g, shb, rr);
+        if (blockIdx.x == 0 && threadIdx.x == 0) record(g, rr, b);
+        if (!(rr > g.ctl->ff * 1e-60)) return;
+    }
+    const double *__restrict__ pv = g.p, *__restrict__ rv = g.r;
     const int64_t s0 = (int64_t)blockIdx.x * kRows;
-    const int nr = (int)min((int64_t)kRows, nrows - s0);
+    const OT *row[kRows];
     double acc[kRows];
 #pragma unroll
-    for (int r = 0; r < kRows; ++r) acc[r] = 0.0;
+    for (int r = 0; r < kRows; ++r) {
+        row[r] = O + min(s0 + r, nrows - 1) * P;
+        acc[r] = 0.0;
+    }
     for (int64_t p = (int64_t)threadIdx.x * VW; p < P; p += (int64_t)kThreads * VW) {
-        double ob[VW], vv[VW];
+        double ob[VW], vv[VW], o[kRows][VW];
 #pragma unroll
         for (int q = 0; q < VW; ++q) {
             ob[q] = obar[p + q];
-            vv[q] = v[p + q];
+            vv[q] = FLY ? fma(b, pv[p + q], rv[p + q]) : pv[p + q];
         }
 #pragma unroll
         for (int r = 0; r < kRows; ++r) {
-            if (r >= nr) break;
-            double o[VW];
-            Vec<OT, VW>::get(O + (s0 + r) * P + p, o);
+            if (kRows > 2 && s0 + r >= nrows) break;
+            Vec<OT, VW>::get(row[r] + p, o[r]);
+            if (kRows <= 2) continue;
 #pragma unroll
-            for (int q = 0; q < VW; ++q) acc[r] = fma(o[q] - ob[q], vv[q], acc[r]);
+            for (int q = 0; q < VW; ++q) acc[r] = fma(o[r][q] - ob[q], vv[q], acc[r]);
         }
+        if (kRows > 2) continue;
+#pragma unroll
+        for (int r = 0; r < kRows; ++r)
+#pragma unroll
+            for (int q = 0; q < VW; ++q) acc[r] = fma(o[r][q] - ob[q], vv[q], acc[r]);
     }
 #pragma unroll
     for (int r = 0; r < kRows; ++r) sh[r][threadIdx.x] = acc[r];
     __syncthreads();
-    for (int off = kThreads / 2; off > 0; off >>= 1) {
-        if (threadIdx.x < off) {
 #pragma unroll
-            for (int r = 0; r < kRows; ++r) sh[r][threadIdx.x] += sh[r][threadIdx.x + off];
-        }
-        __syncthreads();
+    for (int r = 0; r < kRows; ++r) {
+        const double v = tree_sum(sh[r]);
+        if (threadIdx.x == 0 && s0 + r < nrows) u[s0 + r] = v;
     }
-    if (threadIdx.x < nr) u[s0 + threadIdx.x] = sh[threadIdx.x][0];
+}
+
+// p = r + beta p as a launch of its own; block 0 records r.r and beta
+__global__ void __launch_bounds__(kThreads)
+k_update_p(Cg g)
+{
+    __shared__ double sh[kThreads];
+    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    const int64_t k = min(i, g.P - 1);
+    const double pi = g.p[k], ri = g.r[k];   // in flight during the sum
+    if (g.ctl->done) return;
+    double rr;
+    const double b = beta_of(g, sh, rr);
+    if (i < g.P) g.p[i] = fma(b, pi, ri);
+    if (blockIdx.x == 0 && threadIdx.x == 0) record(g, rr, b);
 }
 
 // launches of the two streaming passes, 16-byte loads when P allows them
@@ -160,30 +243,47 @@ template <typename OT>
 constexpr int vec_width() { return 16 / (int)sizeof(OT); }
 
 template <typename OT>
-void launch_colsum(dim3 grid_rows, int64_t P, hipStream_t s, const OT *O, int64_t B,
+void launch_colsum(int64_t nchunk, int64_t P, int n_cu, hipStream_t s, const OT *O, int64_t B,
                    const double *sub, const double *wt, int64_t rpc, double *part,
                    const SrCtl *ctl)
 {
     constexpr int VW = vec_width<OT>();
-    if (P % VW == 0) {
-        const dim3 g((unsigned)((P / VW + kThreads - 1) / kThreads), grid_rows.y);
-        NQS_LAUNCH((k_colsum<OT, VW>), g, dim3(kThreads), 0, s, O, B, P, sub, wt, rpc, part, ctl);
+    if (P % VW == 0 && P / (64 * VW) * nchunk >= 2 * n_cu) {
+        const dim3 g((unsigned)((P / VW + 63) / 64), (unsigned)nchunk);
+        NQS_LAUNCH((k_colsum<OT, VW>), g, dim3(64), 0, s, O, B, P, sub, wt, rpc, part, ctl);
     } else {
-        const dim3 g((unsigned)((P + kThreads - 1) / kThreads), grid_rows.y);
-        NQS_LAUNCH((k_colsum<OT, 1>), g, dim3(kThreads), 0, s, O, B, P, sub, wt, rpc, part, ctl);
+        const dim3 g((unsigned)((P + 63) / 64), (unsigned)nchunk);
+        NQS_LAUNCH((k_colsum<OT, 1>), g, dim3(64), 0, s, O, B, P, sub, wt, rpc, part, ctl);
     }
 }
 
-template <typename OT>
-void launch_rowdot(int64_t nrows, int64_t P, hipStream_t s, const OT *O, const double *obar,
-                   const double *v, double *u, const SrCtl *ctl)
+template <typename OT, int ROWS, bool FLY>
+void launch_rowdot_r(int64_t nrows, hipStream_t s, const OT *O, const double *obar, const Cg &g,
+                     double *u)
 {
     constexpr int VW = vec_width<OT>();
-    const dim3 g((unsigned)((nrows + kRows - 1) / kRows));
-    if (P % VW == 0)
-        NQS_LAUNCH((k_rowdot<OT, VW>), g, dim3(kThreads), 0, s, O, nrows, P, obar, v, u, ctl);
+    const dim3 grid((unsigned)((nrows + ROWS - 1) / ROWS)), th(kThreads);
+    if (g.P % VW == 0)
+        NQS_LAUNCH((k_rowdot<OT, VW, ROWS, FLY>), grid, th, 0, s, O, nrows, obar, g, u);
     else
-        NQS_LAUNCH((k_rowdot<OT, 1>), g, dim3(kThreads), 0, s, O, nrows, P, obar, v, u, ctl);
+        NQS_LAUNCH((k_rowdot<OT, 1, ROWS, FLY>), grid, th, 0, s, O, nrows, obar, g, u);
+}
+
+// Rows a block: four where that leaves two blocks for every CU, else two or one
+// (P = 28,064: 1024 rows 32 us with four, 19 with two; 512 rows 20 with two, 14
+// with one; 19 us before with four).
+template <typename OT>
+void launch_rowdot(int64_t nrows, int n_cu, bool fly, hipStream_t s, const OT *O,
+                   const double *obar, const Cg &g, double *u)
+{
+    if (fly && g.it > 0)
+        launch_rowdot_r<OT, 1, true>(nrows, s, O, obar, g, u);
+    else if (nrows >= (int64_t)8 * n_cu)
+        launch_rowdot_r<OT, 4, false>(nrows, s, O, obar, g, u);
+    else if (nrows >= (int64_t)4 * n_cu)
+        launch_rowdot_r<OT, 2, false>(nrows, s, O, obar, g, u);
+    else
+        launch_rowdot_r<OT, 1, false>(nrows, s, O, obar, g, u);
 }
 
 // partial dot products a.b, one value per block
@@ -217,88 +317,124 @@ k_dot_final(const double *__restrict__ part, int nparts, SrCtl *ctl)
     ctl->done = !(acc > 0.0);
 }
 
-// One CG iteration after Ap's partial column sums, in three launches whose
-// final reductions are repeated by every block that needs them (the same
-// fixed-order sum in every block, so every block sees the same value):
-//   k_ap_dot:     Ap = scale * sum_c part[c] + lam p, and per block sum p.Ap;
-//   k_update_xr2: alpha = r.r / p.Ap; x += alpha p, r -= alpha Ap, and per
-//                 block sum r.r (p.Ap <= 0: stop without updating);
-//   k_update_p2:  beta = r.r_new / r.r; p = r + beta p; block 0 records r.r,
-//                 counts the iteration and stops once ||r|| <= 1e-30 ||F||.
-// r.r of iteration `it` lives in slot it & 1, so block 0 can write the next
-// one while the other blocks still read the current one.
-__device__ double sum_parts(const double *part, int n, double *sh)
-{
-    double acc = 0.0;
-    for (int i = threadIdx.x; i < n; i += kThreads) acc += part[i];
-    return block_sum(acc, sh);
-}
-
+// Ap = scale * sum_c part[c] + lam p, and per block sum p.Ap
 __global__ void __launch_bounds__(kThreads)
-k_ap_dot(const double *__restrict__ part, int nchunk, int64_t P, double scale, double lam,
-         const double *__restrict__ p, double *__restrict__ ap, double *__restrict__ pap_part,
-         const SrCtl *ctl)
+k_ap_dot(const double *__restrict__ part, int nchunk, double scale, double lam, Cg g)
 {
     __shared__ double sh[kThreads];
-    if (ctl->done) return;
+    if (g.ctl->done) return;
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     double d = 0.0;
-    if (i < P) {
+    if (i < g.P) {
         double acc = 0.0;
-        for (int c = 0; c < nchunk; ++c) acc += part[(int64_t)c * P + i];
-        const double v = acc * scale + lam * p[i];
-        ap[i] = v;
-        d = p[i] * v;
+        const double pi = g.p[i];
+#pragma unroll 8
+        for (int c = 0; c < nchunk; ++c) acc += part[(int64_t)c * g.P + i];
+        const double v = fma(acc, scale, lam * pi);
+        g.ap[i] = v;
+        d = pi * v;
     }
     d = block_sum(d, sh);
-    if (threadIdx.x == 0) pap_part[blockIdx.x] = d;
+    if (threadIdx.x == 0) g.pap_part[blockIdx.x] = d;
 }
 
-__global__ void __launch_bounds__(kThreads)
-k_update_xr2(double *__restrict__ x, double *__restrict__ r, const double *__restrict__ p,
-             const double *__restrict__ ap, int64_t n, const double *__restrict__ pap_part,
-             int nparts, double *__restrict__ rr_part, SrCtl *ctl, int it)
+// k_update_p, k_colsum and k_ap_dot in one (k_rowdot has recorded beta), for P
+// up to kSmallP and at most 16 chunks: wave c sums chunk c of 64 columns, the
+// first wave adds the chunks in order.  The columns are 16 of each quarter of a
+// block of kThreads, so that the first two levels of that block's tree over the
+// products p_i (Ap)_i are formed here; the next launch does the rest on the 64
+// values a block that go to pap_part (with the products themselves it waited
+// 3 us longer for them, every block reading all of them).
+constexpr int64_t kSmallP = 16384;
+constexpr int kSmallChunks = 16;
+
+template <typename OT>
+__global__ void __launch_bounds__(64 * kSmallChunks)
+k_ap_small(const OT *__restrict__ O, int64_t B, const double *__restrict__ obar,
+           const double *__restrict__ u, int64_t rows_per_chunk, int nchunk, double scale,
+           double lam, Cg g)
 {
-    __shared__ double sh[kThreads];
-    if (ctl->done) return;
-    const double pap = sum_parts(pap_part, nparts, sh);
+    __shared__ double sh[kSmallChunks][64];
+    const int l = threadIdx.x & 63, c = threadIdx.x >> 6;
+    const int64_t blk = blockIdx.x >> 2;
+    const int m = (blockIdx.x & 3) * 16 + (l & 15);
+    const int64_t i = blk * kThreads + (l >> 4) * 64 + m;
+    const int64_t k0 = min(i, g.P - 1);
+    const double ri = g.r[k0], beta = g.ctl->beta;   // in flight during the sums
+    double pi = g.p[k0];
+    if (g.ctl->done) return;
+    double acc = 0.0;
+    if (i < g.P) {
+        const int64_t s0 = (int64_t)c * rows_per_chunk, s1 = min(B, s0 + rows_per_chunk);
+        const double m = obar[i];
+#pragma unroll 16
+        for (int64_t s = s0; s < s1; ++s) acc = fma((double)O[s * g.P + i] - m, u[s], acc);
+    }
+    sh[c][l] = acc;
+    __syncthreads();
+    if (c > 0) return;
+    double d = 0.0;
+    if (i < g.P) {
+        double sum = 0.0;
+        for (int k = 0; k < nchunk; ++k) sum += sh[k][l];
+        if (g.it > 0) {
+            pi = fma(beta, pi, ri);
+            g.p[i] = pi;
+        }
+        const double v = fma(sum, scale, lam * pi);
+        g.ap[i] = v;
+        d = pi * v;
+    }
+    d += __shfl_down(d, 32, 64);
+    d += __shfl_down(d, 16, 64);
+    if (l < 16) g.pap_part[blk * 64 + m] = d;
+}
+
+// alpha = r.r / p.Ap; x += alpha p, r -= alpha Ap, and per block sum r.r
+// (p.Ap <= 0: stop without updating).  SMALL: pap_part holds 64 values a
+// block and not the block sums; each wave then forms every fourth block's sum.
+template <bool SMALL>
+__global__ void __launch_bounds__(kThreads)
+k_update_xr(Cg g)
+{
+    __shared__ double sh[kThreads], sh2[kThreads];
+    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    const int64_t k = min(i, g.P - 1);
+    const double xi = g.x[k], pi = g.p[k], api = g.ap[k], r0 = g.r[k];   // in flight
+    const double rr = g.ctl->rrv[g.it & 1];
+    if (g.ctl->done) return;
+    double pap;
+    if (SMALL) {
+        sh[threadIdx.x] = 0.0;
+        __syncthreads();
+        const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll 4
+        for (int j = w; j < g.nblk; j += 4) {
+            double v = g.pap_part[j * 64 + l];
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+            if (l == 0) sh[j] = v;
+        }
+        __syncthreads();
+        pap = tree_sum(sh);
+    } else {
+        pap = sum_parts(g.pap_part, g.nblk, sh);
+    }
     if (!(pap > 0.0)) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) ctl->done = 1;
+        if (blockIdx.x == 0 && threadIdx.x == 0) g.ctl->done = 1;
         return;
     }
-    const double a = ctl->rrv[it & 1] / pap;
+    const double a = rr / pap;
     double acc = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * kThreads) {
-        x[i] = fma(a, p[i], x[i]);
-        const double ri = fma(-a, ap[i], r[i]);
-        r[i] = ri;
+    if (i < g.P) {
+        g.x[i] = fma(a, pi, xi);
+        const double ri = fma(-a, api, r0);
+        g.r[i] = ri;
         acc = fma(ri, ri, acc);
     }
-    acc = block_sum(acc, sh);
-    if (threadIdx.x == 0) rr_part[blockIdx.x] = acc;
-    if (blockIdx.x == 0 && threadIdx.x == 0) ctl->alpha = a;
-}
-
-__global__ void __launch_bounds__(kThreads)
-k_update_p2(double *__restrict__ p, const double *__restrict__ r, int64_t n,
-            const double *__restrict__ rr_part, int nparts, SrCtl *ctl, int it)
-{
-    __shared__ double sh[kThreads];
-    if (ctl->done) return;
-    const double rr_new = sum_parts(rr_part, nparts, sh);
-    const double b = rr_new / ctl->rrv[it & 1];
-    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * kThreads)
-        p[i] = fma(b, p[i], r[i]);
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        ctl->rrv[(it + 1) & 1] = rr_new;
-        ctl->rr = rr_new;
-        ctl->beta = b;
-        ctl->it = it + 1;
-        // converged far beyond FP64 resolution: ||r|| <= 1e-30 ||F||
-        if (!(rr_new > ctl->ff * 1e-60)) ctl->done = 1;
-    }
+    acc = block_sum(acc, sh2);
+    if (threadIdx.x == 0) g.rr_part[blockIdx.x] = acc;
+    if (blockIdx.x == 0 && threadIdx.x == 0) g.ctl->alpha = a;
 }
 
 // x = 0, r = p = F
@@ -348,8 +484,18 @@ k_center(const double *__restrict__ e, int64_t B, double *__restrict__ d, SrCtl 
     }
 }
 
-__global__ void k_stats_out(const SrCtl *ctl, double *stats)
+// g.it: the iterations asked for; the last one's r.r is not recorded yet
+__global__ void __launch_bounds__(kThreads)
+k_stats_out(Cg g, double *stats)
 {
+    __shared__ double sh[kThreads];
+    if (g.it > 0 && !g.ctl->done) {
+        double rr;
+        const double b = beta_of(g, sh, rr);
+        if (threadIdx.x == 0) record(g, rr, b);
+    }
+    if (threadIdx.x != 0) return;
+    const SrCtl *ctl = g.ctl;
     stats[0] = ctl->mean;
     stats[1] = ctl->var;
     stats[2] = ctl->ff > 0.0 ? sqrt(ctl->rr / ctl->ff) : 0.0;
@@ -383,7 +529,7 @@ SrLayout layout(int64_t B, int64_t P)
     l.off_ap = take(P);
     l.off_d = take(B);
     l.off_u = take(B);
-    l.off_part = take((size_t)l.nchunk * P);
+    l.off_part = take((size_t)std::max(l.nchunk * P, 64 * l.nblk));   // or k_ap_small's sums
     l.off_dot = take(l.ndot);
     l.off_pap = take(l.nblk);
     l.off_rrp = take(l.nblk);
@@ -392,61 +538,85 @@ SrLayout layout(int64_t B, int64_t P)
     return l;
 }
 
-// The rest of CG iteration `it` once Ap's partial column sums are in `part`.
-void cg_tail(const SrLayout &l, int64_t P, double invB, double lam, double *x, double *r,
-             double *p, double *ap, const double *part, unsigned char *w, SrCtl *ctl, int it,
+// The rest of an iteration once Ap's partial column sums are in `part`.
+void cg_tail(const SrLayout &l, double invB, double lam, const double *part, const Cg &g,
              hipStream_t s)
 {
-    double *pap = (double *)(w + l.off_pap), *rrp = (double *)(w + l.off_rrp);
-    const unsigned nb = (unsigned)l.nblk;
-    NQS_LAUNCH(k_ap_dot, dim3(nb), dim3(kThreads), 0, s, part, (int)l.nchunk, P, invB, lam,
-               (const double *)p, ap, pap, (const SrCtl *)ctl);
-    NQS_LAUNCH(k_update_xr2, dim3(nb), dim3(kThreads), 0, s, x, r, (const double *)p,
-               (const double *)ap, P, (const double *)pap, (int)nb, rrp, ctl, it);
-    NQS_LAUNCH(k_update_p2, dim3(nb), dim3(kThreads), 0, s, p, (const double *)r, P,
-               (const double *)rrp, (int)nb, ctl, it);
+    NQS_LAUNCH(k_ap_dot, dim3(g.nblk), dim3(kThreads), 0, s, part, (int)l.nchunk, invB, lam, g);
+    NQS_LAUNCH(k_update_xr<false>, dim3(g.nblk), dim3(kThreads), 0, s, g);
+}
+
+Cg state(const SrLayout &l, unsigned char *w, int64_t P, double *x)
+{
+    Cg g;
+    g.x = x;
+    g.r = (double *)(w + l.off_r);
+    g.p = (double *)(w + l.off_p);
+    g.ap = (double *)(w + l.off_ap);
+    g.pap_part = (double *)(w + l.off_pap);
+    g.rr_part = (double *)(w + l.off_rrp);
+    g.P = P;
+    g.nblk = (int)l.nblk;
+    g.it = 0;
+    g.ctl = (SrCtl *)(w + l.off_ctl);
+    return g;
+}
+
+// x = 0, r = p = F, and r.r
+void cg_start(const SrLayout &l, const Cg &g, const double *F, double *dot, hipStream_t s)
+{
+    const unsigned vgrid = (unsigned)std::min<int64_t>(1024, l.nblk);
+    NQS_LAUNCH(k_init, dim3(vgrid), dim3(kThreads), 0, s, g.x, g.r, g.p, F, g.P);
+    NQS_LAUNCH(k_dot_part, dim3((unsigned)l.ndot), dim3(kThreads), 0, s, (const double *)g.r,
+               (const double *)g.r, g.P, dot, (const SrCtl *)nullptr);
+    NQS_LAUNCH(k_dot_final, dim3(1), dim3(kThreads), 0, s, (const double *)dot, (int)l.ndot,
+               g.ctl);
 }
 
 template <typename OT>
 void sr_solve_t(const OT *O, const double *e, int64_t B, int64_t P, double lam, int n_iter,
-                double *x, double *stats, unsigned char *w, hipStream_t s)
+                double *x, double *stats, unsigned char *w, int n_cu, hipStream_t s)
 {
     const SrLayout l = layout(B, P);
     double *obar = (double *)(w + l.off_obar), *F = (double *)(w + l.off_F);
-    double *r = (double *)(w + l.off_r), *p = (double *)(w + l.off_p);
-    double *ap = (double *)(w + l.off_ap), *d = (double *)(w + l.off_d);
-    double *u = (double *)(w + l.off_u), *part = (double *)(w + l.off_part);
-    double *dot = (double *)(w + l.off_dot);
-    SrCtl *ctl = (SrCtl *)(w + l.off_ctl);
-    const dim3 cgrid((unsigned)((P + kThreads - 1) / kThreads), (unsigned)l.nchunk);
-    const unsigned vgrid = (unsigned)std::min<int64_t>(1024, (P + kThreads - 1) / kThreads);
-    const unsigned fgrid = (unsigned)((P + kThreads - 1) / kThreads);
+    double *d = (double *)(w + l.off_d), *u = (double *)(w + l.off_u);
+    double *part = (double *)(w + l.off_part), *dot = (double *)(w + l.off_dot);
+    Cg g = state(l, w, P, x);
+    const unsigned fgrid = (unsigned)l.nblk;
     const double invB = 1.0 / (double)B;
 
-    NQS_LAUNCH(k_center, dim3(1), dim3(1024), 0, s, e, B, d, ctl);
+    NQS_LAUNCH(k_center, dim3(1), dim3(1024), 0, s, e, B, d, g.ctl);
     // column means
-    launch_colsum<OT>(cgrid, P, s, O, B, (const double *)nullptr, (const double *)nullptr,
-                      l.rows_per_chunk, part, (const SrCtl *)nullptr);
+    launch_colsum<OT>(l.nchunk, P, n_cu, s, O, B, (const double *)nullptr,
+                      (const double *)nullptr, l.rows_per_chunk, part, (const SrCtl *)nullptr);
     NQS_LAUNCH(k_colsum_final, dim3(fgrid), dim3(kThreads), 0, s, part, (int)l.nchunk, P,
                        invB, 0.0, (const double *)nullptr, obar, (const SrCtl *)nullptr);
     // F = Obar^T (E - Ebar) / B
-    launch_colsum<OT>(cgrid, P, s, O, B, obar, d, l.rows_per_chunk, part,
+    launch_colsum<OT>(l.nchunk, P, n_cu, s, O, B, obar, d, l.rows_per_chunk, part,
                       (const SrCtl *)nullptr);
     NQS_LAUNCH(k_colsum_final, dim3(fgrid), dim3(kThreads), 0, s, part, (int)l.nchunk, P,
                        invB, 0.0, (const double *)nullptr, F, (const SrCtl *)nullptr);
-    NQS_LAUNCH(k_init, dim3(vgrid), dim3(kThreads), 0, s, x, r, p, F, P);
-    NQS_LAUNCH(k_dot_part, dim3((unsigned)l.ndot), dim3(kThreads), 0, s, r, r, P, dot,
-                       (const SrCtl *)nullptr);
-    NQS_LAUNCH(k_dot_final, dim3(1), dim3(kThreads), 0, s, dot, (int)l.ndot, ctl);
-    for (int it = 0; it < n_iter; ++it) {
+    cg_start(l, g, F, dot, s);
+    // (P = 4800, 256 samples: 18.6 us of kernels an iteration against 29; the
+    // blocks of the last launch read P / 4 values each, hence the line at 16 K)
+    const bool small = P <= kSmallP && l.nchunk <= kSmallChunks;
+    if (small) g.pap_part = part;
+    for (; g.it < n_iter; ++g.it) {
         // Ap = Obar^T (Obar p) / B + lambda p
-        launch_rowdot<OT>(B, P, s, O, obar, p, u, ctl);
-        launch_colsum<OT>(cgrid, P, s, O, B, obar, u, l.rows_per_chunk, part, ctl);
-        cg_tail(l, P, invB, lam, x, r, p, ap, part, w, ctl, it, s);
+        if (!small && g.it > 0) NQS_LAUNCH(k_update_p, dim3(fgrid), dim3(kThreads), 0, s, g);
+        launch_rowdot<OT>(B, n_cu, small, s, O, obar, g, u);
+        if (small) {
+            NQS_LAUNCH(k_ap_small<OT>, dim3(4 * fgrid),
+                       dim3(64 * (unsigned)l.nchunk), 0, s, O, B, (const double *)obar,
+                       (const double *)u, l.rows_per_chunk, (int)l.nchunk, invB, lam, g);
+            NQS_LAUNCH(k_update_xr<true>, dim3(fgrid), dim3(kThreads), 0, s, g);
+        } else {
+            launch_colsum<OT>(l.nchunk, P, n_cu, s, O, B, obar, u, l.rows_per_chunk, part, g.ctl);
+            cg_tail(l, invB, lam, part, g, s);
+        }
     }
-    if (stats) NQS_LAUNCH(k_stats_out, dim3(1), dim3(1), 0, s, ctl, stats);
+    if (stats) NQS_LAUNCH(k_stats_out, dim3(1), dim3(kThreads), 0, s, g, stats);
 }
-
 
 // The same solve with O never held whole: rows [r0, r0 + nb) of O are
 // produced on demand into a buffer of `chunk` rows by `rows` (which recomputes
@@ -459,19 +629,16 @@ void sr_solve_t(const OT *O, const double *e, int64_t B, int64_t P, double lam, 
 template <typename OT>
 void sr_solve_rows_t(const SrRows &rows, OT *obuf, int64_t chunk, const double *e, int64_t B,
                      int64_t P, double lam, int n_iter, double *x, double *stats,
-                     unsigned char *w, hipStream_t s)
+                     unsigned char *w, int n_cu, hipStream_t s)
 {
     const SrLayout l = layout(B, P);
     double *obar = (double *)(w + l.off_obar), *F = (double *)(w + l.off_F);
-    double *r = (double *)(w + l.off_r), *p = (double *)(w + l.off_p);
-    double *ap = (double *)(w + l.off_ap), *d = (double *)(w + l.off_d);
-    double *u = (double *)(w + l.off_u), *part = (double *)(w + l.off_part);
-    double *dot = (double *)(w + l.off_dot);
-    SrCtl *ctl = (SrCtl *)(w + l.off_ctl);
+    double *d = (double *)(w + l.off_d), *u = (double *)(w + l.off_u);
+    double *part = (double *)(w + l.off_part), *dot = (double *)(w + l.off_dot);
+    Cg g = state(l, w, P, x);
     const int64_t rpc = l.rows_per_chunk;
     const int64_t nc = (B + chunk - 1) / chunk;
-    const unsigned vgrid = (unsigned)std::min<int64_t>(1024, (P + kThreads - 1) / kThreads);
-    const unsigned fgrid = (unsigned)((P + kThreads - 1) / kThreads);
+    const unsigned fgrid = (unsigned)l.nblk;
     const double invB = 1.0 / (double)B;
     int64_t resident = -1;   // chunk whose rows are in obuf
 
@@ -491,12 +658,11 @@ void sr_solve_rows_t(const SrRows &rows, OT *obuf, int64_t chunk, const double *
     };
     // partial column sums of rows [r0, r0 + nb) into their reduction blocks
     auto colsum = [&](int64_t r0, int nb, const double *sub, const double *wt, const SrCtl *c) {
-        const dim3 g(fgrid, (unsigned)((nb + rpc - 1) / rpc));
-        launch_colsum<OT>(g, P, s, (const OT *)obuf, (int64_t)nb, sub, wt ? wt + r0 : wt, rpc,
-                          part + (r0 / rpc) * P, c);
+        launch_colsum<OT>((nb + rpc - 1) / rpc, P, n_cu, s, (const OT *)obuf, (int64_t)nb, sub,
+                          wt ? wt + r0 : wt, rpc, part + (r0 / rpc) * P, c);
     };
 
-    NQS_LAUNCH(k_center, dim3(1), dim3(1024), 0, s, e, B, d, ctl);
+    NQS_LAUNCH(k_center, dim3(1), dim3(1024), 0, s, e, B, d, g.ctl);
     pass([&](int64_t r0, int nb) {
         colsum(r0, nb, (const double *)nullptr, (const double *)nullptr, (const SrCtl *)nullptr);
     });
@@ -505,18 +671,16 @@ void sr_solve_rows_t(const SrRows &rows, OT *obuf, int64_t chunk, const double *
     pass([&](int64_t r0, int nb) { colsum(r0, nb, obar, d, (const SrCtl *)nullptr); });
     NQS_LAUNCH(k_colsum_final, dim3(fgrid), dim3(kThreads), 0, s, part, (int)l.nchunk, P, invB,
                0.0, (const double *)nullptr, F, (const SrCtl *)nullptr);
-    NQS_LAUNCH(k_init, dim3(vgrid), dim3(kThreads), 0, s, x, r, p, F, P);
-    NQS_LAUNCH(k_dot_part, dim3((unsigned)l.ndot), dim3(kThreads), 0, s, r, r, P, dot,
-               (const SrCtl *)nullptr);
-    NQS_LAUNCH(k_dot_final, dim3(1), dim3(kThreads), 0, s, dot, (int)l.ndot, ctl);
-    for (int it = 0; it < n_iter; ++it) {
+    cg_start(l, g, F, dot, s);
+    for (; g.it < n_iter; ++g.it) {
+        if (g.it > 0) NQS_LAUNCH(k_update_p, dim3(fgrid), dim3(kThreads), 0, s, g);
         pass([&](int64_t r0, int nb) {
-            launch_rowdot<OT>(nb, P, s, (const OT *)obuf, obar, p, u + r0, ctl);
+            launch_rowdot<OT>(nb, n_cu, false, s, (const OT *)obuf, obar, g, u + r0);
         });
-        pass([&](int64_t r0, int nb) { colsum(r0, nb, obar, u, ctl); });
-        cg_tail(l, P, invB, lam, x, r, p, ap, part, w, ctl, it, s);
+        pass([&](int64_t r0, int nb) { colsum(r0, nb, obar, u, g.ctl); });
+        cg_tail(l, invB, lam, part, g, s);
     }
-    if (stats) NQS_LAUNCH(k_stats_out, dim3(1), dim3(1), 0, s, ctl, stats);
+    if (stats) NQS_LAUNCH(k_stats_out, dim3(1), dim3(kThreads), 0, s, g, stats);
 }
 
 }  // namespace
@@ -525,28 +689,28 @@ size_t sr_workspace_bytes(int64_t B, int64_t P) { return layout(B, P).total; }
 
 void launch_sr_solve(const void *O, nqs_dtype odt, const double *e_loc, int64_t B, int64_t P,
                      double lambda, int n_iter, double *x, double *stats, void *work,
-                     hipStream_t s)
+                     int n_cu, hipStream_t s)
 {
     if (odt == NQS_FP32)
         sr_solve_t<float>((const float *)O, e_loc, B, P, lambda, n_iter, x, stats,
-                          (unsigned char *)work, s);
+                          (unsigned char *)work, n_cu, s);
     else
         sr_solve_t<double>((const double *)O, e_loc, B, P, lambda, n_iter, x, stats,
-                           (unsigned char *)work, s);
+                           (unsigned char *)work, n_cu, s);
 }
 
 int64_t sr_row_block(int64_t B) { return layout(B, 1).rows_per_chunk; }
 
 void launch_sr_solve_rows(const SrRows &rows, void *obuf, int64_t chunk, nqs_dtype odt,
                           const double *e_loc, int64_t B, int64_t P, double lambda, int n_iter,
-                          double *x, double *stats, void *work, hipStream_t s)
+                          double *x, double *stats, void *work, int n_cu, hipStream_t s)
 {
     if (odt == NQS_FP32)
         sr_solve_rows_t<float>(rows, (float *)obuf, chunk, e_loc, B, P, lambda, n_iter, x, stats,
-                               (unsigned char *)work, s);
+                               (unsigned char *)work, n_cu, s);
     else
         sr_solve_rows_t<double>(rows, (double *)obuf, chunk, e_loc, B, P, lambda, n_iter, x,
-                                stats, (unsigned char *)work, s);
+                                stats, (unsigned char *)work, n_cu, s);
 }
 
 }  // namespace nqs

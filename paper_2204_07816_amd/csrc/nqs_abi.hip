@@ -1126,7 +1126,8 @@ nqs_status nqs_sr_solve(nqs_ctx *c, const void *O, nqs_dtype odt, const double *
     hipStream_t s = (hipStream_t)stream;
     c->last_stream = s;
     NQS_TRY(ensure(c->ws.sr, sr_workspace_bytes(B, c->P), s));
-    launch_sr_solve(O, odt, e_loc, B, c->P, diag_shift, n_iter, dtheta, stats, c->ws.sr.ptr, s);
+    launch_sr_solve(O, odt, e_loc, B, c->P, diag_shift, n_iter, dtheta, stats, c->ws.sr.ptr,
+                    c->n_cu, s);
     return finish_call();
 }
 
@@ -1152,7 +1153,7 @@ nqs_status nqs_sr_solve_recompute(nqs_ctx *c, const int8_t *spins, nqs_dtype odt
         deriv_rows(cc, spins + r0 * cc->N, nb, dchunk, buf, odt, st);
     };
     launch_sr_solve_rows(rows, c->ws.orows.ptr, chunk, odt, e_loc, B, c->P, diag_shift, n_iter,
-                         dtheta, stats, c->ws.sr.ptr, s);
+                         dtheta, stats, c->ws.sr.ptr, c->n_cu, s);
     return finish_call();
 }
 

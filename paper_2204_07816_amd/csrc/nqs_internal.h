@@ -585,7 +585,7 @@ void launch_mcmc_apply(const nqs_ctx *c, int8_t *spins, int B, const uint32_t *q
 size_t sr_workspace_bytes(int64_t B, int64_t P);
 void launch_sr_solve(const void *O, nqs_dtype odt, const double *e_loc, int64_t B, int64_t P,
                      double lambda, int n_iter, double *x, double *stats, void *work,
-                     hipStream_t s);
+                     int n_cu, hipStream_t s);
 // rows of O recomputed on demand: fills rows [r0, r0 + nb) of O into buf
 // (row-major, nb rows) on the stream
 using SrRows = std::function<void(int64_t r0, int nb, void *buf, hipStream_t s)>;
@@ -594,7 +594,7 @@ using SrRows = std::function<void(int64_t r0, int nb, void *buf, hipStream_t s)>
 int64_t sr_row_block(int64_t B);
 void launch_sr_solve_rows(const SrRows &rows, void *obuf, int64_t chunk, nqs_dtype odt,
                           const double *e_loc, int64_t B, int64_t P, double lambda, int n_iter,
-                          double *x, double *stats, void *work, hipStream_t s);
+                          double *x, double *stats, void *work, int n_cu, hipStream_t s);
 
 inline bool nn_moves(const nqs_ctx *c)
 {

@@ -65,7 +65,8 @@ nqs_status nqs_sr_solve_noalloc(nqs_ctx *c, const void *O, nqs_dtype odt, const 
     if (st != NQS_OK) return st;
     hipStream_t s = (hipStream_t)stream;
     c->last_stream = s;
-    nqs::launch_sr_solve(O, odt, e_loc, B, c->P, diag_shift, n_iter, dtheta, stats, w, s);
+    nqs::launch_sr_solve(O, odt, e_loc, B, c->P, diag_shift, n_iter, dtheta, stats, w, c->n_cu,
+                         s);
     const char *what = nullptr;
     const hipError_t e = nqs::take_launch_error(&what);
     (void)hipGetLastError();
