@@ -793,9 +793,16 @@ k_frame64(FrameArgs a)
     }
 }
 
+// channels of the frame: a ln cosh network's, filled up to 16 or 32 with
+// neurons of zero weight (their ln cosh is 0, so every sum keeps its terms)
+inline int frame_ch(const nqs_ctx *c)
+{
+    return c->net != kNetLnCosh ? c->C : (c->C <= 16 ? 16 : 32);
+}
+
 inline size_t frame_lds(const nqs_ctx *c, int P, bool chains = false)
 {
-    size_t n = (size_t)(c->C / (c->dtype == NQS_FP32 ? 4 : 2)) * plane_bytes16(P) + (size_t)(((P + 2) * (P + 2) + 15) & ~15);
+    size_t n = (size_t)(frame_ch(c) / (c->dtype == NQS_FP32 ? 4 : 2)) * plane_bytes16(P) + (size_t)(((P + 2) * (P + 2) + 15) & ~15);
     if (c->net == kNetCnn2) n += sizeof(double) * ((c->C == 32 ? 2 * (size_t)P * P : 0) + 9 * c->C + 1);
     if (chains) n += (size_t)c->N * (2 * sizeof(double) + 1);
     return (n + 15) & ~(size_t)15;

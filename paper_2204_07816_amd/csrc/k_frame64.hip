@@ -16,21 +16,22 @@ void launch_any(const nqs_ctx *c, const FrameArgs &a, int mode, int64_t items, i
     else if (c->net == kNetCnn2)
         (c->C == 32 ? launch_cnn2_32 : launch_cnn2_16)(c, a, mode, items, shape, s);
     else if (c->dtype == NQS_FP32)
-        (c->C == 32 ? launch_ln32f : launch_ln16f)(c, a, mode, items, shape, s);
+        (frame_ch(c) == 32 ? launch_ln32f : launch_ln16f)(c, a, mode, items, shape, s);
     else
-        (c->C == 32 ? launch_ln32 : launch_ln16)(c, a, mode, items, shape, s);
+        (frame_ch(c) == 32 ? launch_ln32 : launch_ln16)(c, a, mode, items, shape, s);
 }
 
 // The first shape whose waves can form every tile of the largest region at
 // once and of which the LDS holds at least eight waves on a CU (two per SIMD).
 int frame_shape(const nqs_ctx *c, int P, bool regions)
 {
-    const int nhb = c->net == kNetCnn1 ? 1 : c->C / 16;
+    const int C = frame_ch(c);
+    const int nhb = c->net == kNetCnn1 ? 1 : C / 16;
     const int wd = regions ? std::min(c->L, 2 + 2 * (c->net == kNetCnn2 ? 2 * c->K : frame_reach(c)))
                            : c->L;
     const int T = (wd * wd + 15 - (c->dtype == NQS_FP32 ? 0 : 4 * kQuarters)) / 16;
-    const FrameShape *sh = c->C == 16 ? kShapes16 : kShapes32;
-    const int ns = c->C == 16 ? 4 : 3;
+    const FrameShape *sh = C == 16 ? kShapes16 : kShapes32;
+    const int ns = C == 16 ? 4 : 3;
     for (int i = 0; i < ns - 1; ++i) {
         if (c->net == kNetCnn1 && i == 1) continue;      // (not built: two column blocks per wave)
         const int g = sh[i].W / nhb;
@@ -45,13 +46,16 @@ FrameArgs frame_args(const nqs_ctx *c, const int8_t *spins)
 {
     FrameArgs a{};
     a.spins = spins;
-    const int C = c->C;
+    const int C = frame_ch(c);
+    const bool pad = C != c->C;
     if (c->dtype == NQS_FP32) {
-        a.w1 = c->w_vec32;
-        a.w = c->w_vec32 + 10 * C;
+        const float *w = pad ? c->w_pad32 : c->w_vec32;
+        a.w1 = w;
+        a.w = w + 10 * C;
     } else if (c->net == kNetLnCosh) {
-        a.w1 = c->w_vec64;
-        a.w = c->w_vec64 + 10 * C;
+        const double *w = pad ? c->w_pad64 : c->w_vec64;
+        a.w1 = w;
+        a.w = w + 10 * C;
     } else if (c->net == kNetCnn1) {
         a.w1 = c->w_canon;
         a.w = c->w_vec64;
@@ -68,12 +72,40 @@ FrameArgs frame_args(const nqs_ctx *c, const int8_t *spins)
 
 }  // namespace
 
-bool frame64_ok(const nqs_ctx *c)
+static bool frame_fits(const nqs_ctx *c, bool chains = false)
 {
     if (c->dtype != NQS_FP64 && c->dtype != NQS_FP32) return false;
-    if (c->net == kNetCnn1 ? c->C != 16 : (c->C != 16 && c->C != 32)) return false;
     if (c->net == kNetLnCosh && c->K < 2) return false;
-    return frame_lds(c, c->L) <= kLdsMax;
+    return frame_lds(c, c->L, chains) <= kLdsMax;
+}
+
+bool frame64_ok(const nqs_ctx *c)
+{
+    if (c->net == kNetCnn1 ? c->C != 16 : (c->C != 16 && c->C != 32)) return false;
+    return frame_fits(c);
+}
+
+bool frame64_pad_ok(const nqs_ctx *c)
+{
+    return c->net == kNetLnCosh && c->C < 32 && c->C != 16 && frame_fits(c);
+}
+
+// The vector path costs about 1.1e-5 us per channel for each site and layer of
+// a configuration (FP32 0.7e-5), the frame 1.2e-4 us for each that it forms
+// again, whatever the channels: it leads where the region is less than that
+// share of the lattice (FP64, 8 channels: 24x24, 5 layers, share 0.12: 17.9 ->
+// 4.6 ms; 10x10, 4 layers, 0.54: 7.1 -> 5.0 ms; 4 channels, 6x6, 2 layers,
+// 0.72: 0.31 against 0.50 ms).  Short queues are bound by launches, of which
+// the frame needs two (4x4, 2 layers of 4, 4096 pairs: 62 -> 50 us).
+bool frame64_pad_wins(const nqs_ctx *c, int64_t cap)
+{
+    if (cap <= (int64_t)16 * c->n_cu) return true;
+    double inc = 0.0;
+    for (int l = 1; l <= c->K; ++l) {
+        const double e = std::min(2 + 2 * l, c->L);
+        inc += e * e;
+    }
+    return inc < (c->dtype == NQS_FP32 ? 0.06 : 0.09) * c->C * c->K * c->N;
 }
 
 bool frame64_suits(const nqs_ctx *c)
@@ -94,7 +126,7 @@ int64_t frame64_slots(const nqs_ctx *c)
 
 size_t frame64_cache_bytes(const nqs_ctx *c, int64_t cB)
 {
-    return (c->dtype == NQS_FP32 ? sizeof(float) : sizeof(double)) * (size_t)frame64_slots(c) * (size_t)cB * c->N * c->C;
+    return (c->dtype == NQS_FP32 ? sizeof(float) : sizeof(double)) * (size_t)frame64_slots(c) * (size_t)cB * c->N * frame_ch(c);
 }
 
 // samples per cache fill: at most 16 GiB of cached activations
@@ -148,7 +180,16 @@ void frame64_conn(const nqs_ctx *c, const int8_t *spins, const uint32_t *queue,
 
 bool frame64_chains_ok(const nqs_ctx *c)
 {
-    return frame64_ok(c) && frame_lds(c, c->L, true) <= kLdsMax;
+    return frame64_ok(c) && frame_fits(c, true);
+}
+
+// A launch per chain and not per layer and step pays for networks with filled
+// channels until the chains fill the chip several times (6x6, 3 layers of 4, 32
+// steps of 1024 chains: 1.61 -> 0.51 ms).
+bool frame64_pad_chains(const nqs_ctx *c, int64_t B)
+{
+    return frame64_pad_ok(c) && frame_fits(c, true) &&
+           (B <= (int64_t)8 * c->n_cu || frame64_pad_wins(c, B));
 }
 
 void frame64_chains(const nqs_ctx *c, int8_t *spins, int64_t B, int n_steps, const uint32_t *rnd,
@@ -170,12 +211,13 @@ void frame64_chains(const nqs_ctx *c, int8_t *spins, int64_t B, int n_steps, con
     // for eight) while their tiles allow; one wave each where the chains alone
     // fill three waves per SIMD (4096 chains: 3.25 against 3.54 ms).
     const int T = (c->N + 15 - (c->dtype == NQS_FP32 ? 0 : 4 * kQuarters)) / 16;
+    const int C = frame_ch(c);
     int shape = 3;
-    if (c->C == 16 && T <= kShapes16[0].NMAX && B >= 12 * (int64_t)c->n_cu)
+    if (C == 16 && T <= kShapes16[0].NMAX && B >= 12 * (int64_t)c->n_cu)
         shape = 0;
-    else if (c->C == 16 && T <= 4 * kShapes16[2].NMAX)
+    else if (C == 16 && T <= 4 * kShapes16[2].NMAX)
         shape = 2;
-    else if (c->C == 32 && T <= 2 * kShapes32[0].NMAX)
+    else if (C == 32 && T <= 2 * kShapes32[0].NMAX)
         shape = 0;
     launch_any(c, a, kChains, B, shape, s);
 }

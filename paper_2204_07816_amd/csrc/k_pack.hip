@@ -67,6 +67,31 @@ __global__ void k_pack_vec(const double *__restrict__ w, int K, int C, int64_t P
     }
 }
 
+// the vector packing with C channels filled up to Cp by zeros
+template <typename T>
+__global__ void k_pack_pad(const T *__restrict__ v, int K, int C, int Cp, T *__restrict__ out)
+{
+    const int n = 10 * Cp + (K - 1) * (9 * Cp + 1) * Cp;
+    for (int q = blockIdx.x * kThreads + threadIdx.x; q < n; q += gridDim.x * kThreads) {
+        int l = 0, r = q, src = 0;
+        if (r >= 10 * Cp) {
+            r -= 10 * Cp;
+            l = 1 + r / ((9 * Cp + 1) * Cp);
+            r %= (9 * Cp + 1) * Cp;
+            src = 10 * C + (l - 1) * (9 * C + 1) * C;
+        }
+        const int cin = l == 0 ? 1 : C, cinp = l == 0 ? 1 : Cp, co = r % Cp, row = r / Cp;
+        // rows: 9 taps of cinp channels, then the bias
+        const int t = row / cinp, ci = row % cinp;
+        T x = 0;
+        if (co < C && row == 9 * cinp)
+            x = v[src + 9 * cin * C + co];
+        else if (co < C && ci < cin)
+            x = v[src + (t * cin + ci) * C + co];
+        out[q] = x;
+    }
+}
+
 // backward data pass, layers 2..K: [t'][co][ci] = W[co][ci][8 - t']
 __global__ void k_pack_bwd(const double *__restrict__ w, int K, int C, double *__restrict__ bw)
 {
@@ -169,6 +194,18 @@ int grid_of(int64_t n)
 
 }  // namespace
 
+void frame64_pad_pack(const nqs_ctx *c, hipStream_t s)
+{
+    const int Cp = c->C <= 16 ? 16 : 32;
+    const dim3 g(grid_of(10 * Cp + (int64_t)(c->K - 1) * (9 * Cp + 1) * Cp));
+    if (c->dtype == NQS_FP32)
+        NQS_LAUNCH(k_pack_pad<float>, g, dim3(kThreads), 0, s, (const float *)c->w_vec32, c->K,
+                   c->C, Cp, c->w_pad32);
+    else
+        NQS_LAUNCH(k_pack_pad<double>, g, dim3(kThreads), 0, s, (const double *)c->w_vec64, c->K,
+                   c->C, Cp, c->w_pad64);
+}
+
 // every kernel family's packing rebuilt from the canonical vector w_canon
 static void device_repack(nqs_ctx *c, hipStream_t s)
 {
@@ -179,6 +216,7 @@ static void device_repack(nqs_ctx *c, hipStream_t s)
     }
     NQS_LAUNCH(k_pack_vec, dim3(grid_of(c->P)), dim3(kThreads), 0, s, (const double *)c->w_canon,
                K, C, c->P, c->w_vec64, c->w_vec32);
+    if (frame64_pad_ok(c)) frame64_pad_pack(c, s);
     if (K > 1)
         NQS_LAUNCH(k_pack_bwd, dim3(grid_of((int64_t)9 * C * C * (K - 1))), dim3(kThreads), 0, s,
                    (const double *)c->w_canon, K, C, c->w_bwd64);

@@ -153,6 +153,18 @@ nqs_status pack_weights(nqs_ctx *c)
     if ((st = upload(c->w_vec64, v64)) != NQS_OK) return st;
     if ((st = upload(c->w_vec32, v32)) != NQS_OK) return st;
     if ((st = upload(c->w_bwd64, bw)) != NQS_OK) return st;
+    if (frame64_pad_ok(c)) {
+        const int Cp = C <= 16 ? 16 : 32;
+        const size_t n = 10 * Cp + (size_t)(K - 1) * (9 * Cp + 1) * Cp;
+        const bool f32 = c->dtype == NQS_FP32;
+        void **pad = f32 ? (void **)&c->w_pad32 : (void **)&c->w_pad64;
+        if (!*pad && hipMalloc(pad, n * (f32 ? sizeof(float) : sizeof(double))) != hipSuccess) {
+            *pad = nullptr;
+            return NQS_E_NOMEM;
+        }
+        frame64_pad_pack(c, nullptr);
+        HIP_OK(hipDeviceSynchronize());
+    }
     if ((st = upload(c->w_canon, c->w_host)) != NQS_OK) return st;
     if (c->dtype == NQS_BF16 || c->dtype == NQS_BF16X3) {
         // A operands of v_mfma_f32_16x16x32_bf16: lane l holds row m = l % 16
@@ -268,7 +280,7 @@ struct Form {
 Form resolve_form(const nqs_ctx *c, nqs_mode m)
 {
     const nqs_mode r = resolve_mode(c, m);
-    const bool can = c->dtype == NQS_BF16 ? (!c->tuned && incremental_ok(c)) : frame64_ok(c);
+    const bool can = c->dtype == NQS_BF16 ? (!c->tuned && incremental_ok(c)) : (frame64_ok(c) || frame64_pad_ok(c));
     return Form{r, m == NQS_AUTO && r == NQS_FULL && can};
 }
 
@@ -482,7 +494,8 @@ nqs_status log_ratio_stage(nqs_ctx *c, const int8_t *spins, int B, Form form,
     Workspace &w = c->ws;
     const nqs_mode mode = form.mode;
     NQS_TRY(ensure(w.fbase, sizeof(double) * std::max(B, 1), s));
-    if (mode == NQS_FULL && frame64_ok(c))
+    if (mode == NQS_FULL &&
+        (frame64_ok(c) || (form.regions && frame64_pad_ok(c) && frame64_pad_wins(c, cap))))
         return frame_ratio_stage(c, spins, B, form.regions, offsets, dlog, cap, s);
     if (const BlockNet *bn = block_net(c))
         return block_ratio_stage(c, bn, spins, B, mode, offsets, dlog, cap, s);
@@ -872,6 +885,8 @@ nqs_status nqs_destroy(nqs_ctx *c)
     free_dev(c->w_canon);
     free_dev(c->w_vec64);
     free_dev(c->w_vec32);
+    free_dev(c->w_pad64);
+    free_dev(c->w_pad32);
     free_dev(c->w_bwd64);
     free_dev(c->w_mfma);
     free_dev(c->w_mfma_lo);
@@ -961,6 +976,7 @@ nqs_status nqs_reserve(nqs_ctx *c, int64_t B_max, nqs_mode mode)
     // planes are then those of the amplitudes alone
     const bool frame = frame64_ok(c);
     if (frame) NQS_TRY(frame_reserve(c, B, cap, resolve_mode(c, mode) == NQS_FULL, s));
+    if (mode == NQS_AUTO && frame64_pad_ok(c)) NQS_TRY(frame_reserve(c, B, cap, true, s));
     const int64_t work = frame ? B : std::max<int64_t>(cap, B);
     if (const BlockNet *bn = block_net(c)) {
         const int64_t chunk = bn->chunk(c, work);
@@ -1172,7 +1188,7 @@ nqs_status nqs_mcmc(nqs_ctx *c, int8_t *spins, int64_t B, int32_t n_steps,
     const nqs_mode m = form.mode;
     if (m == NQS_INCREMENTAL && c->dtype == NQS_BF16X3 && !incremental_ok(c))
         return NQS_E_UNSUPPORTED;
-    if (frame64_chains_ok(c)) {
+    if (frame64_chains_ok(c) || frame64_pad_chains(c, B)) {
         // FP64: every step in one launch (the forms give the same ratios)
         frame64_chains(c, spins, B, n_steps, rand_bond, rand_u, accepted, s);
         return finish_call();

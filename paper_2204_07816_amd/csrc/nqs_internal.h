@@ -240,6 +240,8 @@ struct nqs_ctx {
     double *w_canon = nullptr;    // device canonical FP64 [P]
     double *w_vec64 = nullptr;    // vector-path packing, FP64
     float *w_vec32 = nullptr;     // vector-path packing, FP32
+    double *w_pad64 = nullptr;    // the same with channels filled up (frame64.h)
+    float *w_pad32 = nullptr;
     double *w_bwd64 = nullptr;    // transposed packing for the backward data pass
     uint16_t *w_mfma = nullptr;   // BF16 MFMA A-operand packing, layers 2..K
     uint16_t *w_mfma_lo = nullptr;  // BF16X3: the lo parts of the same packing
@@ -334,6 +336,13 @@ void vec_base_forward_cached(const nqs_ctx *c, const int8_t *spins, int nb, doub
 // frame64_suits: CNN1's cone is faster here than in k_c1_cone.
 bool frame64_ok(const nqs_ctx *c);
 bool frame64_suits(const nqs_ctx *c);
+// frame64_pad_ok: a ln cosh network of other than 16 or 32 channels, served with
+// channels filled up; frame64_pad_wins: faster so for a queue of up to cap items;
+// frame64_pad_chains: for B Metropolis chains.
+bool frame64_pad_ok(const nqs_ctx *c);
+bool frame64_pad_wins(const nqs_ctx *c, int64_t cap);
+bool frame64_pad_chains(const nqs_ctx *c, int64_t B);
+void frame64_pad_pack(const nqs_ctx *c, hipStream_t s);   // w_pad from w_vec (k_pack.hip)
 int64_t frame64_slots(const nqs_ctx *c);
 size_t frame64_cache_bytes(const nqs_ctx *c, int64_t cB);
 void frame64_base(const nqs_ctx *c, const int8_t *spins, int64_t cB, int64_t b0, int64_t nb,
