@@ -89,6 +89,7 @@ struct Params {
     uint16_t *cache_out;     // [B][K-1][N][C] bf16 (physical slots)
     double *hsum_out;        // [B][N]
     double *f_out;           // [B]
+    const int32_t *redo;     // [B], or null: samples with 0 keep their outputs
     // exchanged configurations
     const uint32_t *queue;
     const int64_t *qlen;
@@ -141,6 +142,7 @@ k_net(NetJobs jobs)
         int s, x0 = 0, y0 = 0, w0 = 1, h0 = 1, qi = -1, qj = -1;
         if (base) {
             s = (int)unit;
+            if (prm.redo && !prm.redo[s]) continue;
         } else {
             const uint32_t e = prm.queue[unit];
             s = item_sample(e);
@@ -488,7 +490,7 @@ size_t mfma_cache_bytes(const nqs_ctx *c, int64_t B)
 }
 
 void mfma_base_forward(const nqs_ctx *c, const int8_t *spins, int B, double *f, double *hsum,
-                       void *cache, hipStream_t s)
+                       void *cache, const int32_t *redo, hipStream_t s)
 {
     if (B <= 0) return;
     Params p = common(c, spins, kBase);
@@ -496,6 +498,7 @@ void mfma_base_forward(const nqs_ctx *c, const int8_t *spins, int B, double *f, 
     p.cache_out = (uint16_t *)cache;
     p.hsum_out = hsum;
     p.f_out = f;
+    p.redo = redo;
     const int grid = std::min(B, c->n_cu * 2);
     launch(c, true, dim3(grid), p, s);
 }

@@ -157,7 +157,7 @@ __device__ __forceinline__ void with_count(int n, Fn &&f)
 
 // W waves form a configuration; PK > 1 (W = 1 only): PK waves of a workgroup,
 // each with its own configurations and no barrier between them
-template <int C, int W, int PK, int NMAX, int EU>
+template <int C, int W, int PK, int NMAX, int EU, bool FEW>
 __global__ void __launch_bounds__(W * PK * 64, EU)
 k_frame_bf16(BfJobs jobs)
 {
@@ -243,6 +243,40 @@ k_frame_bf16(BfJobs jobs)
             sf[q] = a.spins[(int64_t)s * N0 + site];
         }
         sync();
+        // ring R_{k+2} \ R_k from the sample's activations of layer k.  Few
+        // configurations (FEW) wait for each round of loads, so the whole ring
+        // is one or two: the rows beyond R_k, then the columns beside it (14x14,
+        // 5 layers of 16, 357 configurations: 21.6 us by rows, 16.4 so).
+        auto ring_once = [&](int k) {
+            const Region in = region(k), out = region(k + 2);
+            const int eh = out.h - in.h, ew = out.w - in.w;
+            const int nrow = eh * out.w, total = (nrow + ew * in.h) * CHK;
+            // beyond R_k's end first, two where the ring has two sides
+            const int hb = out.h == P ? eh : 2, wb = out.w == P ? ew : 2;
+            const uint32_t mw = ((1u << 20) + out.w - 1) / out.w, me = ew ? ((1u << 20) + ew - 1) / ew : 0;
+            const uint16_t *src = cache_s + (int64_t)(k - 1) * N0 * C + 8 * (tid % CHK);
+            auto entry = [&](int q, int &f) {
+                const int e = (q < total ? q : 0) / CHK;
+                int fx, fy;
+                if (e < nrow) {
+                    const int v = (int)(((uint32_t)e * mw) >> 20);
+                    fy = v < hb ? inside(in.y0 + in.h + v) : inside(out.y0 + v - hb);
+                    fx = inside(out.x0 + e - v * out.w);
+                } else {
+                    const int v = (int)(((uint32_t)(e - nrow) * me) >> 20), h = e - nrow - v * ew;
+                    fy = inside(in.y0 + v);
+                    fx = h < wb ? inside(in.x0 + in.w + h) : inside(out.x0 + h - wb);
+                }
+                f = (fy * P + fx) * 16 + (tid % CHK) * SB;
+                return *(const u32x4 *)(src + (lat(fy, ay) * L + lat(fx, ax)) * C);
+            };
+            for (int q = tid; q < total; q += 2 * NT) {       // (NT is a multiple of CHK)
+                int f0, f1;
+                const u32x4 d0 = entry(q, f0), d1 = entry(q + NT, f1);
+                *(u32x4 *)(fr + f0) = d0;
+                if (q + NT < total) *(u32x4 *)(fr + f1) = d1;
+            }
+        };
         // layer 1 on R_1 (vector ALU): thread (site, lane group's channels)
         {
             const uint32_t mul = ((1u << 20) + r1.w - 1) / r1.w;
@@ -272,10 +306,9 @@ k_frame_bf16(BfJobs jobs)
                     *(uint2 *)(to + (gg >> 1) * SB + (gg & 1) * 8) = uint2{w[0], w[1]};
             }
         }
-        // ring R_{k+2} \ R_k from the sample's activations of layer k: the
-        // threads span a stretch of a row (site, chunk), the rows are taken
-        // four at a time
-        auto ring = [&](int k) {
+        // the ring where configurations are many: the threads span a stretch of a row
+        // (site, chunk), the rows are taken four at a time
+        auto ring_rows = [&](int k) {
             constexpr int XP = NT / CHK;
             const Region in = region(k), out = region(k + 2);
             if (in.w == out.w && in.h == out.h) return;
@@ -308,6 +341,10 @@ k_frame_bf16(BfJobs jobs)
                     if (o3) *(u32x4 *)(fc + f3 * P * 16) = d3;
                 }
             }
+        };
+        auto ring = [&](int k) {
+            if constexpr (FEW) ring_once(k);
+            else ring_rows(k);
         };
         ring(1);
         sync();
@@ -427,10 +464,10 @@ size_t frame_bytes(const nqs_ctx *c)
            ~(size_t)15;
 }
 
-template <int C, int W, int PK, int NMAX, int EU>
+template <int C, int W, int PK, int NMAX, int EU, bool FEW = false>
 void launch_w(const BfJobs &jobs, int n_cu, int64_t items, hipStream_t s)
 {
-    const auto kernel = k_frame_bf16<C, W, PK, NMAX, EU>;
+    const auto kernel = k_frame_bf16<C, W, PK, NMAX, EU, FEW>;
     const int lds = jobs.lds * PK;
     (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     int occ = 1;
@@ -490,11 +527,14 @@ void mfma_inc_forward_jobs(const ConnJob *jobs, int n, hipStream_t s)
     // channels: one sample 62 us with one wave and 55 with four, two 63 and 57,
     // four (1600 configurations) 65 and 70
     const bool one = tiles <= 16 && 8 * lds <= kLdsMax && items >= (int64_t)4 * n_cu;
+    const bool few = tiles <= 24 && items < (int64_t)4 * n_cu;
     if (jobs[0].c->C == 32) {
         if (one && tiles <= 9)
             launch_w<32, 1, 4, 9, 3>(jp, n_cu, items, s);
         else if (one)
             launch_w<32, 1, 4, 16, 2>(jp, n_cu, items, s);
+        else if (few)
+            launch_w<32, 4, 1, 6, 3, true>(jp, n_cu, items, s);
         else if (tiles <= 24)
             launch_w<32, 4, 1, 6, 3>(jp, n_cu, items, s);
         else
@@ -504,6 +544,8 @@ void mfma_inc_forward_jobs(const ConnJob *jobs, int n, hipStream_t s)
             launch_w<16, 1, 4, 9, 4>(jp, n_cu, items, s);
         else if (one)
             launch_w<16, 1, 4, 16, 3>(jp, n_cu, items, s);
+        else if (few)
+            launch_w<16, 4, 1, 6, 4, true>(jp, n_cu, items, s);
         else if (tiles <= 24)
             launch_w<16, 4, 1, 6, 4>(jp, n_cu, items, s);
         else

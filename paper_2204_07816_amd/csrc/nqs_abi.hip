@@ -335,7 +335,8 @@ size_t cache_bytes(const nqs_ctx *c, int64_t B)
 
 // BF16 / BF16X3 base pass: log-amplitudes, per-site sums and the activation
 // cache of the samples, in the context's workspace.
-nqs_status bf16_base_stage(nqs_ctx *c, const int8_t *spins, int B, hipStream_t s)
+nqs_status bf16_base_stage(nqs_ctx *c, const int8_t *spins, int B, hipStream_t s,
+                           const int32_t *redo = nullptr)
 {
     Workspace &w = c->ws;
     NQS_TRY(ensure(w.fbase, sizeof(double) * std::max(B, 1), s));
@@ -346,7 +347,7 @@ nqs_status bf16_base_stage(nqs_ctx *c, const int8_t *spins, int B, hipStream_t s
                         nullptr, s);
     else
         mfma_base_forward(c, spins, B, (double *)w.fbase.ptr, (double *)w.hsum.ptr, w.cache.ptr,
-                          s);
+                          redo, s);
     return NQS_OK;
 }
 
@@ -487,9 +488,11 @@ nqs_status block_ratio_stage(nqs_ctx *c, const BlockNet *bn, const int8_t *spins
 }
 
 // Base pass + exchanged-configuration pass: dlog[item].  offsets: the queue
-// offsets of the samples (null: one item per sample).
+// offsets of the samples (null: one item per sample).  redo (BF16, or null):
+// samples with 0 there are as they were in the previous call.
 nqs_status log_ratio_stage(nqs_ctx *c, const int8_t *spins, int B, Form form,
-                           const int64_t *offsets, double *dlog, int64_t cap, hipStream_t s)
+                           const int64_t *offsets, double *dlog, int64_t cap, hipStream_t s,
+                           const int32_t *redo = nullptr)
 {
     Workspace &w = c->ws;
     const nqs_mode mode = form.mode;
@@ -517,7 +520,7 @@ nqs_status log_ratio_stage(nqs_ctx *c, const int8_t *spins, int B, Form form,
         return NQS_OK;
     }
     if (c->dtype == NQS_BF16) {
-        NQS_TRY(bf16_base_stage(c, spins, B, s));
+        NQS_TRY(bf16_base_stage(c, spins, B, s, redo));
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (c->timing) {
             (void)hipEventCreate(&e0);
@@ -988,6 +991,7 @@ nqs_status nqs_reserve(nqs_ctx *c, int64_t B_max, nqs_mode mode)
             NQS_TRY(ensure(w.cache, bn->cache_bytes(c, B), s));
     } else if (c->dtype == NQS_BF16) {
         NQS_TRY(ensure(w.cache, cache_bytes(c, B), s));
+        NQS_TRY(ensure(w.flags, sizeof(int32_t) * std::max(B, 1), s));
     } else if (c->dtype == NQS_BF16X3) {
         NQS_TRY(ensure(w.cache, cache_bytes(c, B), s));
         if (resolve_mode(c, mode) == NQS_FULL) NQS_TRY(x3_full_reserve(c, x3_chunk(c, cap), s));
@@ -1025,7 +1029,8 @@ nqs_status nqs_log_psi(nqs_ctx *c, const int8_t *spins, int64_t B, double *log_a
         }
     } else if (c->dtype == NQS_BF16) {
         NQS_TRY(ensure(w.cache, cache_bytes(c, B), s));
-        mfma_base_forward(c, spins, (int)B, log_abs, (double *)w.hsum.ptr, w.cache.ptr, s);
+        mfma_base_forward(c, spins, (int)B, log_abs, (double *)w.hsum.ptr, w.cache.ptr, nullptr,
+                          s);
     } else if (c->dtype == NQS_BF16X3) {
         NQS_TRY(ensure(w.cache, cache_bytes(c, B), s));
         x3_base_forward(c, spins, (int)B, log_abs, (double *)w.hsum.ptr, w.cache.ptr, nullptr, s);
@@ -1216,10 +1221,18 @@ nqs_status nqs_mcmc(nqs_ctx *c, int8_t *spins, int64_t B, int32_t n_steps,
         }
         return finish_call();
     }
+    // BF16: a chain's base pass is repeated only after a step that moved it (14x14,
+    // 5 layers of 16, 357 chains: the base pass was 35 us of a step's 58)
+    int32_t *moved = nullptr;
+    if (c->dtype == NQS_BF16) {
+        NQS_TRY(ensure(w.flags, sizeof(int32_t) * B, s));
+        moved = (int32_t *)w.flags.ptr;
+    }
     for (int32_t t = 0; t < n_steps; ++t) {
         launch_mcmc_propose(c, (int)B, rand_bond + (int64_t)t * B, queue, qlen, s);
-        NQS_TRY(log_ratio_stage(c, spins, (int)B, form, nullptr, dlog, B, s));
-        launch_mcmc_decide(c, spins, (int)B, queue, dlog, rand_u + (int64_t)t * B, nullptr,
+        NQS_TRY(log_ratio_stage(c, spins, (int)B, form, nullptr, dlog, B, s,
+                                t > 0 ? moved : nullptr));
+        launch_mcmc_decide(c, spins, (int)B, queue, dlog, rand_u + (int64_t)t * B, moved,
                            accepted, true, s);
     }
     return finish_call();

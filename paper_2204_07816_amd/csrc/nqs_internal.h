@@ -406,8 +406,9 @@ struct ConnJob {
 // --- MFMA (BF16) network kernels (k_conv_mfma.hip) ---
 bool mfma_supported(const nqs_ctx *c);
 size_t mfma_cache_bytes(const nqs_ctx *c, int64_t B);
+// redo ([B], or null): samples with 0 there keep the outputs that they have
 void mfma_base_forward(const nqs_ctx *c, const int8_t *spins, int B, double *f, double *hsum,
-                       void *cache, hipStream_t s);
+                       void *cache, const int32_t *redo, hipStream_t s);
 // mode: NQS_FULL or NQS_INCREMENTAL.  Items [0, qlen[0]) of the queue.
 void mfma_conn_forward(const nqs_ctx *c, nqs_mode mode, const int8_t *spins,
                        const uint32_t *queue, const int64_t *qlen, int64_t capacity,

@@ -70,3 +70,25 @@ def test_chains_by_regions(L, K, C):
         acc = ctx.mcmc(s, rb, ru, mode=mode)
         out.append((s.cpu().numpy(), acc.cpu().numpy()))
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("L,K,C,B,mode", [(4, 2, 16, 3, "auto"), (14, 3, 16, 70, "auto"),
+                                          (12, 6, 32, 40, "incremental"), (8, 5, 32, 40, "full")])
+def test_chains_keep_base_pass(L, K, C, B, mode):
+    # many steps in one call (the base pass follows the chains that move) against
+    # one call a step
+    steps = 24
+    w = inputs.stress_weights(K, C, 0.3, 45)
+    sp = inputs.spins_any(L, B, 46)
+    g = np.random.default_rng(47)
+    rb = torch.as_tensor(g.integers(0, 4 * L * L, (steps, B)).astype(np.int32)).cuda()
+    ru = torch.as_tensor(g.random((steps, B))).cuda()
+    ctx = nqs.Context(L, 1.0, 0.5, K, C, w, "bf16")
+    one, each = torch.as_tensor(sp).cuda(), torch.as_tensor(sp).cuda()
+    acc = ctx.mcmc(one, rb, ru, mode=mode)
+    acc2 = torch.zeros_like(acc)
+    for t in range(steps):
+        ctx.mcmc(each, rb[t:t + 1], ru[t:t + 1], accepted=acc2, mode=mode)
+    print(L, K, C, B, mode, "accepted", int(acc.sum()), "of", steps * B, flush=True)
+    assert torch.equal(one, each) and torch.equal(acc, acc2)
+    assert 0 < int(acc.sum()) < steps * B
