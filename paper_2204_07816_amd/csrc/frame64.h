@@ -816,10 +816,27 @@ inline int frame_reach(const nqs_ctx *c)
     return c->net == kNetLnCosh ? c->K : (c->net == kNetCnn1 ? 2 * c->K : 2 * c->K + 1);
 }
 
+// Tiles of the largest layer: the whole torus, or with `regions` the pair's box
+// widened by the stored layers' reach.  FP64's last few sites go to quarter tiles.
+inline int frame_tiles(const nqs_ctx *c, bool regions)
+{
+    const int S = c->net == kNetLnCosh ? c->K : 2 * c->K;
+    const int wd = regions ? std::min(c->L, 2 + 2 * S) : c->L;
+    return (wd * wd + 15 - (c->dtype == NQS_FP32 ? 0 : 4 * kQuarters)) / 16;
+}
+
+// tiles that W waves of NMAX each can form
+inline int frame_room(const nqs_ctx *c, int W, int NMAX)
+{
+    return W / (c->net == kNetCnn1 ? 1 : frame_ch(c) / 16) * NMAX;
+}
+
 template <typename T, int C, int NET, int W, int PK, int NMAX, int MODE, int EU>
 void launch_w(const nqs_ctx *c, FrameArgs a, int64_t items, hipStream_t s)
 {
     const auto kernel = k_frame64<T, C, NET, W, PK, NMAX, MODE, EU>;
+    if (frame_tiles(c, MODE == kItems && a.regions) > frame_room(c, W, NMAX))
+        return refuse_launch("k_frame64: more tiles than the waves can form");
     a.lds = (int)frame_lds(c, a.P, MODE == kChains);
     const int lds = a.lds * PK;
     (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);

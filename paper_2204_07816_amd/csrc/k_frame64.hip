@@ -26,16 +26,12 @@ void launch_any(const nqs_ctx *c, const FrameArgs &a, int mode, int64_t items, i
 int frame_shape(const nqs_ctx *c, int P, bool regions)
 {
     const int C = frame_ch(c);
-    const int nhb = c->net == kNetCnn1 ? 1 : C / 16;
-    const int wd = regions ? std::min(c->L, 2 + 2 * (c->net == kNetCnn2 ? 2 * c->K : frame_reach(c)))
-                           : c->L;
-    const int T = (wd * wd + 15 - (c->dtype == NQS_FP32 ? 0 : 4 * kQuarters)) / 16;
+    const int T = frame_tiles(c, regions);
     const FrameShape *sh = C == 16 ? kShapes16 : kShapes32;
     const int ns = C == 16 ? 4 : 3;
     for (int i = 0; i < ns - 1; ++i) {
         if (c->net == kNetCnn1 && i == 1) continue;      // (not built: two column blocks per wave)
-        const int g = sh[i].W / nhb;
-        if ((T + g - 1) / g > sh[i].NMAX) continue;
+        if (T > frame_room(c, sh[i].W, sh[i].NMAX)) continue;
         if ((int)(kLdsMax / (frame_lds(c, P) * sh[i].PK)) * sh[i].W * sh[i].PK < 8) continue;
         return i;
     }
@@ -72,11 +68,18 @@ FrameArgs frame_args(const nqs_ctx *c, const int8_t *spins)
 
 }  // namespace
 
+// The torus frame has to fit the LDS and its tiles the widest shape (the base
+// pass's, and the last of items and chains): FP32 frames of half the size would
+// reach 35x35 sites of 32 channels and 50x50 of 16, but 8 waves hold 40 and 80
+// tiles, lattices up to 24x24 and 34x34.
 static bool frame_fits(const nqs_ctx *c, bool chains = false)
 {
     if (c->dtype != NQS_FP64 && c->dtype != NQS_FP32) return false;
     if (c->net == kNetLnCosh && c->K < 2) return false;
-    return frame_lds(c, c->L, chains) <= kLdsMax;
+    const FrameShape w = kShapes16[3];
+    static_assert(kShapes16[3].W == kShapes32[2].W && kShapes16[3].NMAX == kShapes32[2].NMAX,
+                  "one widest shape");
+    return frame_lds(c, c->L, chains) <= kLdsMax && frame_tiles(c, false) <= frame_room(c, w.W, w.NMAX);
 }
 
 bool frame64_ok(const nqs_ctx *c)
@@ -210,14 +213,15 @@ void frame64_chains(const nqs_ctx *c, int8_t *spins, int64_t B, int n_steps, con
     // of 16, 32 steps of 512 chains: 0.65 ms against 1.17 for one wave and 0.82
     // for eight) while their tiles allow; one wave each where the chains alone
     // fill three waves per SIMD (4096 chains: 3.25 against 3.54 ms).
-    const int T = (c->N + 15 - (c->dtype == NQS_FP32 ? 0 : 4 * kQuarters)) / 16;
+    const int T = frame_tiles(c, false);
+    auto holds = [&](const FrameShape &s) { return T <= frame_room(c, s.W, s.NMAX); };
     const int C = frame_ch(c);
     int shape = 3;
-    if (C == 16 && T <= kShapes16[0].NMAX && B >= 12 * (int64_t)c->n_cu)
+    if (C == 16 && holds(kShapes16[0]) && B >= 12 * (int64_t)c->n_cu)
         shape = 0;
-    else if (C == 16 && T <= 4 * kShapes16[2].NMAX)
+    else if (C == 16 && holds(kShapes16[2]))
         shape = 2;
-    else if (C == 32 && T <= 2 * kShapes32[0].NMAX)
+    else if (C == 32 && holds(kShapes32[0]))
         shape = 0;
     launch_any(c, a, kChains, B, shape, s);
 }

@@ -614,9 +614,8 @@ thread_local hipError_t g_launch_err = hipSuccess;
 thread_local const char *g_launch_what = nullptr;
 }  // namespace
 
-void note_launch(const char *what)
+static void keep_launch_error(hipError_t e, const char *what)
 {
-    const hipError_t e = hipGetLastError();
     if (e != hipSuccess && g_launch_err == hipSuccess) {
         g_launch_err = e;
         g_launch_what = what;
@@ -624,6 +623,10 @@ void note_launch(const char *what)
             std::fprintf(stderr, "libnqs: launch of %s failed: %s\n", what, hipGetErrorString(e));
     }
 }
+
+void note_launch(const char *what) { keep_launch_error(hipGetLastError(), what); }
+
+void refuse_launch(const char *what) { keep_launch_error(hipErrorInvalidValue, what); }
 
 hipError_t take_launch_error(const char **what)
 {

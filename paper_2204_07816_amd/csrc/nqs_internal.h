@@ -273,6 +273,7 @@ namespace nqs {
 // successful call, so every launch is checked right away and the first
 // failure of a call is kept (thread-local) until the API entry point returns.
 void note_launch(const char *what);
+void refuse_launch(const char *what);   // the same for a launch that its host side rules out
 hipError_t take_launch_error(const char **what);
 
 #define NQS_LAUNCH(kernel, ...)                     \
@@ -332,7 +333,8 @@ void vec_base_forward_cached(const nqs_ctx *c, const int8_t *spins, int nb, doub
 // gives dlog (and isign) of those samples' queue items (offsets: [B + 1] queue
 // offsets, null: item s belongs to sample s) among items 0 .. cap - 1; with a
 // null cache every neuron is recomputed, else those the exchange can change.
-// frame64_ok: the L x L frame fits (FULL, and AUTO where it resolves to FULL);
+// frame64_ok: the L x L frame fits the LDS and its tiles the widest workgroup
+// shape (FULL, and AUTO where it resolves to FULL);
 // frame64_suits: CNN1's cone is faster here than in k_c1_cone.
 bool frame64_ok(const nqs_ctx *c);
 bool frame64_suits(const nqs_ctx *c);
