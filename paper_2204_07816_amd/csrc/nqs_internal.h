@@ -48,7 +48,8 @@ __device__ inline double sgpr(double c)
     return c;
 }
 
-// expm1(-2a) for a >= 0 (any a; NaN gives a finite value): k = rint(x log2 e)
+// expm1(-2a) for a >= 0 (any a; NaN gives a finite value, which the callers'
+// sums or selections with a make NaN again): k = rint(x log2 e)
 // from the low bits of x log2 e + 1.5 2^52, r = x - k ln 2 in two parts, the
 // near-minimax degree-9 fit of (expm1 r - r) / r^2 on |r| <= ln 2 / 2, and
 // 2^k (1 + p) - 1.  Below x = -80 expm1 is -1 to the last bit.
@@ -107,7 +108,7 @@ __device__ inline double ln_cosh_of(double a, double m)
     return a + fma(s2 * w, q, s2);
 }
 
-// ln cosh z and tanh z from one expm1, for the forward pass of the backward
+// ln cosh z and tanh z (NaN for NaN) from one expm1, for the forward pass of the backward
 // (which keeps tanh z, the derivative of ln cosh, for the data gradient):
 // tanh|z| = -m / (2 + m) at full relative precision, and ln cosh z to a few
 // ulp of |z| in absolute terms (the pass needs ln cosh only as the next
@@ -117,7 +118,7 @@ __device__ inline double ln_cosh_tanh(double z, double *th)
 {
     const double a = fabs(z);
     const double m = expm1_m2(a);
-    *th = copysign(-m / (2.0 + m), z);
+    *th = z == z ? copysign(-m / (2.0 + m), z) : z;
     return ln_cosh_of(a, m);
 }
 
