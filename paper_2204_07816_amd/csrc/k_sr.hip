@@ -22,10 +22,16 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kMaxChunks = 64;
 
+// No launch writes a flag that it reads: the waves of a block have to agree on
+// it before their barriers.  done[it & 1] is written by the first launch of
+// iteration it (k_dot_final for it = 0) and read by the others of that
+// iteration; stop is written by the last and read by the first of the next.
 struct SrCtl {
     double rr, ff, alpha, beta, mean, var;
     double rrv[2];   // r.r at the start of iteration it, in slot it & 1
-    int done, it;
+    int done[2];     // no work left in iteration it, in slot it & 1
+    int stop;        // p.Ap <= 0: nothing after that iteration
+    int it;
 };
 
 __device__ inline double ld(const float *p, int64_t i) { return (double)p[i]; }
@@ -82,9 +88,9 @@ template <typename OT, int VW>
 __global__ void __launch_bounds__(64)
 k_colsum(const OT *__restrict__ O, int64_t B, int64_t P, const double *__restrict__ sub,
          const double *__restrict__ wt, int64_t rows_per_chunk, double *__restrict__ part,
-         const SrCtl *ctl)
+         const int *done)
 {
-    if (ctl && ctl->done) return;
+    if (done && *done) return;
     const int64_t p = ((int64_t)blockIdx.x * 64 + threadIdx.x) * VW;
     if (p >= P) return;
     const int64_t s0 = (int64_t)blockIdx.y * rows_per_chunk;
@@ -110,9 +116,8 @@ k_colsum(const OT *__restrict__ O, int64_t B, int64_t P, const double *__restric
 // out[p] = scale * sum_c part[c][p] (+ lam * v[p])
 __global__ void k_colsum_final(const double *__restrict__ part, int nchunk, int64_t P,
                                double scale, double lam, const double *__restrict__ v,
-                               double *__restrict__ out, const SrCtl *ctl)
+                               double *__restrict__ out)
 {
-    if (ctl && ctl->done) return;
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= P) return;
     double acc = 0.0;
@@ -135,7 +140,18 @@ struct Cg {
     int64_t P;
     int nblk, it;
     SrCtl *ctl;
+
+    __host__ __device__ const int *done() const { return &ctl->done[it & 1]; }
 };
+
+// For the first launch of iteration g.it > 0: whether an earlier one was the
+// last.  `first`: the thread that passes that on to this iteration's launches.
+__device__ __forceinline__ bool over(const Cg &g, bool first)
+{
+    const bool end = g.ctl->done[(g.it - 1) & 1] || g.ctl->stop;
+    if (end && first) g.ctl->done[g.it & 1] = 1;
+    return end;
+}
 
 // beta of iteration g.it > 0 from the previous one's partials of r.r.  r.r of
 // the state before iteration i lives in slot i & 1, so a recording block can
@@ -154,7 +170,7 @@ __device__ __forceinline__ void record(const Cg &g, double rr, double beta)
     g.ctl->rr = rr;
     g.ctl->beta = beta;
     g.ctl->it = g.it;
-    if (!(rr > g.ctl->ff * 1e-60)) g.ctl->done = 1;
+    g.ctl->done[g.it & 1] = !(rr > g.ctl->ff * 1e-60);
 }
 
 // First launch of an iteration: u[s] = sum_p (O[s][p] - obar[p]) v[p].  FLY:
@@ -174,7 +190,7 @@ k_rowdot(const OT *__restrict__ O, int64_t nrows, const double *__restrict__ oba
 {
     __shared__ double sh[kRows][kThreads];
     __shared__ double shb[kThreads];
-    if (g.ctl->done) return;
+    if (FLY ? over(g, blockIdx.x == 0 && threadIdx.x == 0) : *g.done() != 0) return;
     const int64_t P = g.P;
     double b = 0.0;
     if (FLY) {
@@ -231,7 +247,7 @@ k_update_p(Cg g)
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     const int64_t k = min(i, g.P - 1);
     const double pi = g.p[k], ri = g.r[k];   // in flight during the sum
-    if (g.ctl->done) return;
+    if (over(g, i == 0)) return;
     double rr;
     const double b = beta_of(g, sh, rr);
     if (i < g.P) g.p[i] = fma(b, pi, ri);
@@ -245,15 +261,15 @@ constexpr int vec_width() { return 16 / (int)sizeof(OT); }
 template <typename OT>
 void launch_colsum(int64_t nchunk, int64_t P, int n_cu, hipStream_t s, const OT *O, int64_t B,
                    const double *sub, const double *wt, int64_t rpc, double *part,
-                   const SrCtl *ctl)
+                   const int *done)
 {
     constexpr int VW = vec_width<OT>();
     if (P % VW == 0 && P / (64 * VW) * nchunk >= 2 * n_cu) {
         const dim3 g((unsigned)((P / VW + 63) / 64), (unsigned)nchunk);
-        NQS_LAUNCH((k_colsum<OT, VW>), g, dim3(64), 0, s, O, B, P, sub, wt, rpc, part, ctl);
+        NQS_LAUNCH((k_colsum<OT, VW>), g, dim3(64), 0, s, O, B, P, sub, wt, rpc, part, done);
     } else {
         const dim3 g((unsigned)((P + 63) / 64), (unsigned)nchunk);
-        NQS_LAUNCH((k_colsum<OT, 1>), g, dim3(64), 0, s, O, B, P, sub, wt, rpc, part, ctl);
+        NQS_LAUNCH((k_colsum<OT, 1>), g, dim3(64), 0, s, O, B, P, sub, wt, rpc, part, done);
     }
 }
 
@@ -289,10 +305,9 @@ void launch_rowdot(int64_t nrows, int n_cu, bool fly, hipStream_t s, const OT *O
 // partial dot products a.b, one value per block
 __global__ void __launch_bounds__(kThreads)
 k_dot_part(const double *__restrict__ a, const double *__restrict__ b, int64_t n,
-           double *__restrict__ part, const SrCtl *ctl)
+           double *__restrict__ part)
 {
     __shared__ double sh[kThreads];
-    if (ctl && ctl->done) return;
     double acc = 0.0;
     for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * kThreads)
@@ -314,7 +329,8 @@ k_dot_final(const double *__restrict__ part, int nparts, SrCtl *ctl)
     ctl->rrv[0] = acc;
     ctl->ff = acc;
     ctl->it = 0;
-    ctl->done = !(acc > 0.0);
+    ctl->stop = 0;
+    ctl->done[0] = !(acc > 0.0);
 }
 
 // Ap = scale * sum_c part[c] + lam p, and per block sum p.Ap
@@ -322,7 +338,7 @@ __global__ void __launch_bounds__(kThreads)
 k_ap_dot(const double *__restrict__ part, int nchunk, double scale, double lam, Cg g)
 {
     __shared__ double sh[kThreads];
-    if (g.ctl->done) return;
+    if (*g.done()) return;
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     double d = 0.0;
     if (i < g.P) {
@@ -362,7 +378,7 @@ k_ap_small(const OT *__restrict__ O, int64_t B, const double *__restrict__ obar,
     const int64_t k0 = min(i, g.P - 1);
     const double ri = g.r[k0], beta = g.ctl->beta;   // in flight during the sums
     double pi = g.p[k0];
-    if (g.ctl->done) return;
+    if (*g.done()) return;
     double acc = 0.0;
     if (i < g.P) {
         const int64_t s0 = (int64_t)c * rows_per_chunk, s1 = min(B, s0 + rows_per_chunk);
@@ -402,7 +418,7 @@ k_update_xr(Cg g)
     const int64_t k = min(i, g.P - 1);
     const double xi = g.x[k], pi = g.p[k], api = g.ap[k], r0 = g.r[k];   // in flight
     const double rr = g.ctl->rrv[g.it & 1];
-    if (g.ctl->done) return;
+    if (*g.done()) return;
     double pap;
     if (SMALL) {
         sh[threadIdx.x] = 0.0;
@@ -421,7 +437,7 @@ k_update_xr(Cg g)
         pap = sum_parts(g.pap_part, g.nblk, sh);
     }
     if (!(pap > 0.0)) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) g.ctl->done = 1;
+        if (blockIdx.x == 0 && threadIdx.x == 0) g.ctl->stop = 1;
         return;
     }
     const double a = rr / pap;
@@ -479,8 +495,6 @@ k_center(const double *__restrict__ e, int64_t B, double *__restrict__ d, SrCtl 
     if (threadIdx.x == 0) {
         ctl->mean = mean;
         ctl->var = sh[0] / (double)B;
-        ctl->done = 0;
-        ctl->it = 0;
     }
 }
 
@@ -489,7 +503,7 @@ __global__ void __launch_bounds__(kThreads)
 k_stats_out(Cg g, double *stats)
 {
     __shared__ double sh[kThreads];
-    if (g.it > 0 && !g.ctl->done) {
+    if (g.it > 0 && !over(g, false)) {
         double rr;
         const double b = beta_of(g, sh, rr);
         if (threadIdx.x == 0) record(g, rr, b);
@@ -568,7 +582,7 @@ void cg_start(const SrLayout &l, const Cg &g, const double *F, double *dot, hipS
     const unsigned vgrid = (unsigned)std::min<int64_t>(1024, l.nblk);
     NQS_LAUNCH(k_init, dim3(vgrid), dim3(kThreads), 0, s, g.x, g.r, g.p, F, g.P);
     NQS_LAUNCH(k_dot_part, dim3((unsigned)l.ndot), dim3(kThreads), 0, s, (const double *)g.r,
-               (const double *)g.r, g.P, dot, (const SrCtl *)nullptr);
+               (const double *)g.r, g.P, dot);
     NQS_LAUNCH(k_dot_final, dim3(1), dim3(kThreads), 0, s, (const double *)dot, (int)l.ndot,
                g.ctl);
 }
@@ -588,14 +602,14 @@ void sr_solve_t(const OT *O, const double *e, int64_t B, int64_t P, double lam, 
     NQS_LAUNCH(k_center, dim3(1), dim3(1024), 0, s, e, B, d, g.ctl);
     // column means
     launch_colsum<OT>(l.nchunk, P, n_cu, s, O, B, (const double *)nullptr,
-                      (const double *)nullptr, l.rows_per_chunk, part, (const SrCtl *)nullptr);
+                      (const double *)nullptr, l.rows_per_chunk, part, (const int *)nullptr);
     NQS_LAUNCH(k_colsum_final, dim3(fgrid), dim3(kThreads), 0, s, part, (int)l.nchunk, P,
-                       invB, 0.0, (const double *)nullptr, obar, (const SrCtl *)nullptr);
+                       invB, 0.0, (const double *)nullptr, obar);
     // F = Obar^T (E - Ebar) / B
     launch_colsum<OT>(l.nchunk, P, n_cu, s, O, B, obar, d, l.rows_per_chunk, part,
-                      (const SrCtl *)nullptr);
+                      (const int *)nullptr);
     NQS_LAUNCH(k_colsum_final, dim3(fgrid), dim3(kThreads), 0, s, part, (int)l.nchunk, P,
-                       invB, 0.0, (const double *)nullptr, F, (const SrCtl *)nullptr);
+                       invB, 0.0, (const double *)nullptr, F);
     cg_start(l, g, F, dot, s);
     // (P = 4800, 256 samples: 18.6 us of kernels an iteration against 29; the
     // blocks of the last launch read P / 4 values each, hence the line at 16 K)
@@ -611,7 +625,8 @@ void sr_solve_t(const OT *O, const double *e, int64_t B, int64_t P, double lam, 
                        (const double *)u, l.rows_per_chunk, (int)l.nchunk, invB, lam, g);
             NQS_LAUNCH(k_update_xr<true>, dim3(fgrid), dim3(kThreads), 0, s, g);
         } else {
-            launch_colsum<OT>(l.nchunk, P, n_cu, s, O, B, obar, u, l.rows_per_chunk, part, g.ctl);
+            launch_colsum<OT>(l.nchunk, P, n_cu, s, O, B, obar, u, l.rows_per_chunk, part,
+                              g.done());
             cg_tail(l, invB, lam, part, g, s);
         }
     }
@@ -657,27 +672,27 @@ void sr_solve_rows_t(const SrRows &rows, OT *obuf, int64_t chunk, const double *
         }
     };
     // partial column sums of rows [r0, r0 + nb) into their reduction blocks
-    auto colsum = [&](int64_t r0, int nb, const double *sub, const double *wt, const SrCtl *c) {
+    auto colsum = [&](int64_t r0, int nb, const double *sub, const double *wt, const int *done) {
         launch_colsum<OT>((nb + rpc - 1) / rpc, P, n_cu, s, (const OT *)obuf, (int64_t)nb, sub,
-                          wt ? wt + r0 : wt, rpc, part + (r0 / rpc) * P, c);
+                          wt ? wt + r0 : wt, rpc, part + (r0 / rpc) * P, done);
     };
 
     NQS_LAUNCH(k_center, dim3(1), dim3(1024), 0, s, e, B, d, g.ctl);
     pass([&](int64_t r0, int nb) {
-        colsum(r0, nb, (const double *)nullptr, (const double *)nullptr, (const SrCtl *)nullptr);
+        colsum(r0, nb, (const double *)nullptr, (const double *)nullptr, (const int *)nullptr);
     });
     NQS_LAUNCH(k_colsum_final, dim3(fgrid), dim3(kThreads), 0, s, part, (int)l.nchunk, P, invB,
-               0.0, (const double *)nullptr, obar, (const SrCtl *)nullptr);
-    pass([&](int64_t r0, int nb) { colsum(r0, nb, obar, d, (const SrCtl *)nullptr); });
+               0.0, (const double *)nullptr, obar);
+    pass([&](int64_t r0, int nb) { colsum(r0, nb, obar, d, (const int *)nullptr); });
     NQS_LAUNCH(k_colsum_final, dim3(fgrid), dim3(kThreads), 0, s, part, (int)l.nchunk, P, invB,
-               0.0, (const double *)nullptr, F, (const SrCtl *)nullptr);
+               0.0, (const double *)nullptr, F);
     cg_start(l, g, F, dot, s);
     for (; g.it < n_iter; ++g.it) {
         if (g.it > 0) NQS_LAUNCH(k_update_p, dim3(fgrid), dim3(kThreads), 0, s, g);
         pass([&](int64_t r0, int nb) {
             launch_rowdot<OT>(nb, n_cu, false, s, (const OT *)obuf, obar, g, u + r0);
         });
-        pass([&](int64_t r0, int nb) { colsum(r0, nb, obar, u, g.ctl); });
+        pass([&](int64_t r0, int nb) { colsum(r0, nb, obar, u, g.done()); });
         cg_tail(l, invB, lam, part, g, s);
     }
     if (stats) NQS_LAUNCH(k_stats_out, dim3(1), dim3(kThreads), 0, s, g, stats);
