@@ -158,8 +158,8 @@ void frame64_base(const nqs_ctx *c, const int8_t *spins, int64_t cB, int64_t b0,
 
 void frame64_conn(const nqs_ctx *c, const int8_t *spins, const uint32_t *queue,
                   const int64_t *offsets, int64_t cap, int64_t cB, int64_t b0, int64_t nb,
-                  const void *cache, const double *site, const int32_t *neg, double *dlog,
-                  int8_t *isign, hipStream_t s)
+                  const void *cache, const double *site, const int32_t *neg, const double *f,
+                  double *dlog, int8_t *isign, hipStream_t s)
 {
     if (nb <= 0 || cap <= 0) return;
     FrameArgs a = frame_args(c, spins);
@@ -169,6 +169,7 @@ void frame64_conn(const nqs_ctx *c, const int8_t *spins, const uint32_t *queue,
     a.cache = const_cast<void *>(cache);
     a.site = const_cast<double *>(site);
     a.neg = const_cast<int32_t *>(neg);
+    a.f = const_cast<double *>(f);
     a.cB = cB;
     a.b0 = b0;
     a.nb = nb;

@@ -423,8 +423,8 @@ nqs_status frame_ratio_stage(nqs_ctx *c, const int8_t *spins, int B, bool region
                      (double *)w.fbase.ptr, (int8_t *)w.sgn.ptr, s);
         if (c->timing && b0 == 0) (void)hipEventRecord(e0, s);
         frame64_conn(c, spins, (const uint32_t *)w.queue.ptr, offsets, cap, chunk, b0, nb, cache,
-                     (const double *)w.hsum.ptr, (const int32_t *)w.hneg.ptr, dlog,
-                     (int8_t *)w.isign.ptr, s);
+                     (const double *)w.hsum.ptr, (const int32_t *)w.hneg.ptr,
+                     (const double *)w.fbase.ptr, dlog, (int8_t *)w.isign.ptr, s);
     }
     if (c->timing) {
         (void)hipEventRecord(e1, s);
@@ -470,7 +470,8 @@ nqs_status block_ratio_stage(nqs_ctx *c, const BlockNet *bn, const int8_t *spins
         const double *cache = (const double *)w.cache.ptr;
         const double *site = cache + frame64_slots(c) * B * c->N * c->C;
         frame64_conn(c, spins, (const uint32_t *)w.queue.ptr, offsets, cap, B, 0, B, cache, site,
-                     (const int32_t *)(site + (int64_t)B * c->N), dlog, (int8_t *)w.isign.ptr, s);
+                     (const int32_t *)(site + (int64_t)B * c->N), nullptr, dlog,
+                     (int8_t *)w.isign.ptr, s);
     } else if (cone)
         bn->cone_forward(c, spins, B, (const uint32_t *)w.queue.ptr, (const int64_t *)w.qlen.ptr,
                          cap, (const double *)w.cache.ptr, dlog, (int8_t *)w.isign.ptr, s);
@@ -553,8 +554,8 @@ nqs_status log_ratio_stage(nqs_ctx *c, const int8_t *spins, int B, Form form,
                                     (double *)w.cache.ptr, chunk, s);
             if (c->timing && b0 == 0) (void)hipEventRecord(e0, s);
             frame64_conn(c, spins, (const uint32_t *)w.queue.ptr, offsets, cap, chunk, b0, nb,
-                         (const double *)w.cache.ptr, (const double *)w.hsum.ptr, nullptr, dlog,
-                         nullptr, s);
+                         (const double *)w.cache.ptr, (const double *)w.hsum.ptr, nullptr, nullptr,
+                         dlog, nullptr, s);
         }
         if (c->timing) {
             (void)hipEventRecord(e1, s);
