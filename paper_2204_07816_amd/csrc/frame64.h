@@ -94,7 +94,7 @@ struct FrameArgs {
     void *cache;                // [slots][cB][N][C] of samples b0 .., in the frame's chunks
     double *site;               // [B][N] per-site terms of the samples
     int32_t *neg;               // [B][N] negative output neurons per site (block networks)
-    double *f;                  // base pass: [B] log-amplitude; items (may be null): the samples'
+    double *f;                  // base pass: [B] log-amplitude
     int8_t *sgn;                // base pass: [B] network sign
     int64_t cB, b0, nb;         // cache slot stride; samples of this launch
     double *dlog;               // [cap]
@@ -349,7 +349,6 @@ k_frame64(FrameArgs a)
     double un = 0.0, un_next = 0.0;
     for (; u < u_end;) {
         int s, qi = -1, qj = -1, ax = 0, ay = 0, w0 = 2, h0 = 2;
-        double f0 = 0.0;                     // the sample's log-amplitude
         if constexpr (MODE != kItems) {
             s = (int)(a.b0 + u);
             if constexpr (CHAIN) {
@@ -393,7 +392,6 @@ k_frame64(FrameArgs a)
             const int b = item_bond(e), tau = b & 3, i0 = b >> 2;
             const int xi = i0 % L, yi = i0 / L;
             s = item_sample(e);
-            if (a.f) f0 = a.f[s];
             qi = i0;
             qj = wrap1(yi + bond_dy(tau), L) * L + wrap1(xi + bond_dx(tau), L);
             ax = xi;
@@ -781,19 +779,6 @@ k_frame64(FrameArgs a)
                     v += red[w];
                     if constexpr (NET != kNetLnCosh) ng += nred[w];
                 }
-            if (MODE == kItems && part && !isfinite(f0)) {
-                // a neuron that is 0 (or infinite) outside the region is so in S'
-                // too, and the ratio undefined as in the full recomputation
-                const int l = NET == kNetCnn2 ? S + 1 : S;
-                const Region r = region(l);
-                for (int q = 0; q < N; ++q) {
-                    const int dx = wrap1(q % L - wrap1(ax - l, L), L), dy = wrap1(q / L - wrap1(ay - l, L), L);
-                    if ((r.w < L && dx >= r.w) || (r.h < L && dy >= r.h)) {
-                        const double t = a.site[(int64_t)s * N + q];
-                        v += t - t;
-                    }
-                }
-            }
             if (!isfinite(v)) atomicOr(a.err, kErrNonFinite);
             const int8_t sg = (ng & 1) ? -1 : 1;
             if constexpr (BASE) {

@@ -19,8 +19,8 @@ constexpr int kThreads = 256;
 __global__ void __launch_bounds__(kThreads)
 k_energy_reduce(const int64_t *__restrict__ offsets, const uint32_t *__restrict__ queue,
                 const double *__restrict__ dlog, const int8_t *__restrict__ isign,
-                const double *__restrict__ ediag, double J1, double J2, int marshall,
-                double *__restrict__ e_loc, int32_t *err)
+                const double *__restrict__ ediag, const double *__restrict__ f, double J1,
+                double J2, int marshall, double *__restrict__ e_loc, int32_t *err)
 {
     __shared__ double red[kThreads];
     const int s = blockIdx.x;
@@ -41,7 +41,8 @@ k_energy_reduce(const int64_t *__restrict__ offsets, const uint32_t *__restrict_
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        const double e = ediag[s] + red[0];
+        double e = ediag[s] + red[0];
+        if (f) e += f[s] - f[s];
         if (!isfinite(e)) atomicOr(err, kErrNonFinite);
         e_loc[s] = e;
     }
@@ -53,7 +54,7 @@ __global__ void __launch_bounds__(kThreads)
 k_energy_reduce_tj(const int8_t *__restrict__ spins, int L, const int64_t *__restrict__ offsets,
                    const uint32_t *__restrict__ queue, const double *__restrict__ dlog,
                    const int8_t *__restrict__ isign, const double *__restrict__ ediag,
-                   double t_hop, double J, int marshall, double *__restrict__ e_loc, int32_t *err)
+                   const double *__restrict__ f, double t_hop, double J, int marshall, double *__restrict__ e_loc, int32_t *err)
 {
     __shared__ uint16_t pre[kMaxSites + 1];   // pre[k] = electrons on sites 0 .. k-1
     __shared__ int scan[kThreads];
@@ -109,7 +110,8 @@ k_energy_reduce_tj(const int8_t *__restrict__ spins, int L, const int64_t *__res
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        const double e = ediag[s] + red[0];
+        double e = ediag[s] + red[0];
+        if (f) e += f[s] - f[s];
         if (!isfinite(e)) atomicOr(err, kErrNonFinite);
         e_loc[s] = e;
     }
@@ -152,15 +154,16 @@ k_energy_stats(const double *__restrict__ e, int B, double *__restrict__ stats)
 
 void launch_energy_reduce(const nqs_ctx *c, const int8_t *spins, int B, const int64_t *offsets,
                           const uint32_t *queue, const double *dlog, const int8_t *isign,
-                          const double *ediag, double *e_loc, int32_t *err, hipStream_t s)
+                          const double *ediag, const double *f, double *e_loc, int32_t *err,
+                          hipStream_t s)
 {
     if (B <= 0) return;
     if (c->model == kModelTJ)
         NQS_LAUNCH(k_energy_reduce_tj, dim3(B), dim3(kThreads), 0, s, spins, c->L, offsets,
-                   queue, dlog, isign, ediag, c->t_hop, c->J1, c->marshall, e_loc, err);
+                   queue, dlog, isign, ediag, f, c->t_hop, c->J1, c->marshall, e_loc, err);
     else
         NQS_LAUNCH(k_energy_reduce, dim3(B), dim3(kThreads), 0, s, offsets, queue, dlog,
-                   isign, ediag, c->J1, c->J2, c->marshall, e_loc, err);
+                   isign, ediag, f, c->J1, c->J2, c->marshall, e_loc, err);
 }
 
 void launch_energy_stats(const double *e_loc, int B, double *stats, hipStream_t s)

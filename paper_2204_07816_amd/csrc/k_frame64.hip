@@ -66,7 +66,44 @@ FrameArgs frame_args(const nqs_ctx *c, const int8_t *spins)
     return a;
 }
 
+// A sample whose amplitude is 0 (or infinite): a neuron outside an item's region
+// (the pair's box widened by S sites) is 0 in S' too, and the ratio undefined as
+// in the full recomputation.  A workgroup per sample; others leave at once.
+constexpr int kZeroThreads = 64;
+
+__global__ void __launch_bounds__(kZeroThreads)
+k_frame_zeros(const uint32_t *__restrict__ queue, const int64_t *__restrict__ offsets, int64_t cap,
+              int L, int S, const double *__restrict__ site, const double *__restrict__ f,
+              double *__restrict__ dlog)
+{
+    const int64_t s = blockIdx.x;
+    if (isfinite(f[s])) return;
+    const int64_t q1 = min(offsets ? offsets[s + 1] : s + 1, cap);
+    for (int64_t u = (offsets ? offsets[s] : s) + threadIdx.x; u < q1; u += kZeroThreads) {
+        const int b = item_bond(queue[u]), tau = b & 3, x = (b >> 2) % L, y = (b >> 2) / L;
+        const int w = (tau == 1 ? 1 : 2) + 2 * S, h = (tau == 0 ? 1 : 2) + 2 * S;
+        const int x0 = x - S, y0 = y - S - (tau == 3 ? 1 : 0);
+        double v = dlog[u];
+        for (int p = 0; p < L * L; ++p) {
+            const int dx = ((p % L - x0) % L + L) % L, dy = ((p / L - y0) % L + L) % L;
+            if (dx >= w || dy >= h) {
+                const double t = site[s * L * L + p];
+                v += t - t;
+            }
+        }
+        dlog[u] = v;
+    }
+}
+
 }  // namespace
+
+void frame64_zeros(const nqs_ctx *c, const uint32_t *queue, const int64_t *offsets, int64_t cap,
+                   int64_t B, const double *site, const double *f, double *dlog, hipStream_t s)
+{
+    if (B <= 0 || cap <= 0) return;
+    NQS_LAUNCH(k_frame_zeros, dim3((unsigned)B), dim3(kZeroThreads), 0, s, queue, offsets, cap, c->L,
+               frame_reach(c), site, f, dlog);
+}
 
 // The torus frame has to fit the LDS and its tiles the widest shape (the base
 // pass's, and the last of items and chains): FP32 frames of half the size would
@@ -158,8 +195,8 @@ void frame64_base(const nqs_ctx *c, const int8_t *spins, int64_t cB, int64_t b0,
 
 void frame64_conn(const nqs_ctx *c, const int8_t *spins, const uint32_t *queue,
                   const int64_t *offsets, int64_t cap, int64_t cB, int64_t b0, int64_t nb,
-                  const void *cache, const double *site, const int32_t *neg, const double *f,
-                  double *dlog, int8_t *isign, hipStream_t s)
+                  const void *cache, const double *site, const int32_t *neg, double *dlog,
+                  int8_t *isign, hipStream_t s)
 {
     if (nb <= 0 || cap <= 0) return;
     FrameArgs a = frame_args(c, spins);
@@ -169,7 +206,6 @@ void frame64_conn(const nqs_ctx *c, const int8_t *spins, const uint32_t *queue,
     a.cache = const_cast<void *>(cache);
     a.site = const_cast<double *>(site);
     a.neg = const_cast<int32_t *>(neg);
-    a.f = const_cast<double *>(f);
     a.cB = cB;
     a.b0 = b0;
     a.nb = nb;

@@ -423,8 +423,8 @@ nqs_status frame_ratio_stage(nqs_ctx *c, const int8_t *spins, int B, bool region
                      (double *)w.fbase.ptr, (int8_t *)w.sgn.ptr, s);
         if (c->timing && b0 == 0) (void)hipEventRecord(e0, s);
         frame64_conn(c, spins, (const uint32_t *)w.queue.ptr, offsets, cap, chunk, b0, nb, cache,
-                     (const double *)w.hsum.ptr, (const int32_t *)w.hneg.ptr,
-                     (const double *)w.fbase.ptr, dlog, (int8_t *)w.isign.ptr, s);
+                     (const double *)w.hsum.ptr, (const int32_t *)w.hneg.ptr, dlog,
+                     (int8_t *)w.isign.ptr, s);
     }
     if (c->timing) {
         (void)hipEventRecord(e1, s);
@@ -470,8 +470,7 @@ nqs_status block_ratio_stage(nqs_ctx *c, const BlockNet *bn, const int8_t *spins
         const double *cache = (const double *)w.cache.ptr;
         const double *site = cache + frame64_slots(c) * B * c->N * c->C;
         frame64_conn(c, spins, (const uint32_t *)w.queue.ptr, offsets, cap, B, 0, B, cache, site,
-                     (const int32_t *)(site + (int64_t)B * c->N), nullptr, dlog,
-                     (int8_t *)w.isign.ptr, s);
+                     (const int32_t *)(site + (int64_t)B * c->N), dlog, (int8_t *)w.isign.ptr, s);
     } else if (cone)
         bn->cone_forward(c, spins, B, (const uint32_t *)w.queue.ptr, (const int64_t *)w.qlen.ptr,
                          cap, (const double *)w.cache.ptr, dlog, (int8_t *)w.isign.ptr, s);
@@ -554,8 +553,8 @@ nqs_status log_ratio_stage(nqs_ctx *c, const int8_t *spins, int B, Form form,
                                     (double *)w.cache.ptr, chunk, s);
             if (c->timing && b0 == 0) (void)hipEventRecord(e0, s);
             frame64_conn(c, spins, (const uint32_t *)w.queue.ptr, offsets, cap, chunk, b0, nb,
-                         (const double *)w.cache.ptr, (const double *)w.hsum.ptr, nullptr, nullptr,
-                         dlog, nullptr, s);
+                         (const double *)w.cache.ptr, (const double *)w.hsum.ptr, nullptr, dlog,
+                         nullptr, s);
         }
         if (c->timing) {
             (void)hipEventRecord(e1, s);
@@ -586,6 +585,14 @@ nqs_status log_ratio_stage(nqs_ctx *c, const int8_t *spins, int B, Form form,
         c->events.push_back({e0, e1});
     }
     return NQS_OK;
+}
+
+// The samples' log-amplitudes where log_ratio_stage took a block network's ratios
+// by regions, in which a zero amplitude does not show; else null.
+const double *zeros_of(const nqs_ctx *c, Form form)
+{
+    return block_net(c) && form.regions && form.mode == NQS_FULL ? (const double *)c->ws.fbase.ptr
+                                                                 : nullptr;
 }
 
 // Status of the kernels enqueued by one API call (launch errors only; device
@@ -1071,7 +1078,7 @@ nqs_status nqs_local_energy(nqs_ctx *c, const int8_t *spins, int64_t B, double *
     launch_energy_reduce(c, spins, (int)B, (int64_t *)c->ws.offsets.ptr,
                          (uint32_t *)c->ws.queue.ptr, (double *)c->ws.dlog.ptr,
                          block_net(c) ? (const int8_t *)c->ws.isign.ptr : nullptr,
-                         (double *)c->ws.ediag.ptr, e_loc, c->err, s);
+                         (double *)c->ws.ediag.ptr, zeros_of(c, m), e_loc, c->err, s);
     return finish_call();
 }
 
@@ -1089,7 +1096,11 @@ nqs_status nqs_log_ratios(nqs_ctx *c, const int8_t *spins, int64_t B, nqs_mode m
     c->last_stream = s;
     if (B == 0) return NQS_OK;
     NQS_TRY(integer_stage(c, spins, (int)B, s));
-    NQS_TRY(log_ratio_stage(c, spins, (int)B, m, (const int64_t *)c->ws.offsets.ptr, dlog, cap, s));
+    const int64_t *off = (const int64_t *)c->ws.offsets.ptr;
+    NQS_TRY(log_ratio_stage(c, spins, (int)B, m, off, dlog, cap, s));
+    if (const double *f = zeros_of(c, m))
+        frame64_zeros(c, (const uint32_t *)c->ws.queue.ptr, off, cap, B, (const double *)c->ws.hsum.ptr,
+                      f, dlog, s);
     return finish_call();
 }
 
@@ -1236,6 +1247,8 @@ nqs_status nqs_mcmc(nqs_ctx *c, int8_t *spins, int64_t B, int32_t n_steps,
         launch_mcmc_propose(c, (int)B, rand_bond + (int64_t)t * B, queue, qlen, s);
         NQS_TRY(log_ratio_stage(c, spins, (int)B, form, nullptr, dlog, B, s,
                                 t > 0 ? moved : nullptr));
+        if (const double *f = zeros_of(c, form))
+            frame64_zeros(c, queue, nullptr, B, B, (const double *)w.hsum.ptr, f, dlog, s);
         launch_mcmc_decide(c, spins, (int)B, queue, dlog, rand_u + (int64_t)t * B, moved,
                            accepted, true, s);
     }
@@ -1316,7 +1329,7 @@ nqs_status nqs_local_energy_multi(const nqs_eloc_job *jobs, int32_t n, nqs_mode 
         if (jobs[i].B == 0) continue;
         launch_energy_reduce(c, jobs[i].spins, (int)jobs[i].B, (int64_t *)c->ws.offsets.ptr,
                              (uint32_t *)c->ws.queue.ptr, (double *)c->ws.dlog.ptr, nullptr,
-                             (double *)c->ws.ediag.ptr, jobs[i].e_loc, c->err, s);
+                             (double *)c->ws.ediag.ptr, nullptr, jobs[i].e_loc, c->err, s);
     }
     return finish_call();
 }

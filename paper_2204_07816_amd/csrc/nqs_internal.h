@@ -333,8 +333,7 @@ void vec_base_forward_cached(const nqs_ctx *c, const int8_t *spins, int nb, doub
 // activations of frame64_slots layers, [slots][cB][N][C].  The exchanged pass
 // gives dlog (and isign) of those samples' queue items (offsets: [B + 1] queue
 // offsets, null: item s belongs to sample s) among items 0 .. cap - 1; with a
-// null cache every neuron is recomputed, else those the exchange can change;
-// f (the samples' log-amplitudes, or null) lets a zero of the others show.
+// null cache every neuron is recomputed, else those the exchange can change.
 // frame64_ok: the L x L frame fits the LDS and its tiles the widest workgroup
 // shape (FULL, and AUTO where it resolves to FULL);
 // frame64_suits: CNN1's cone is faster here than in k_c1_cone.
@@ -354,8 +353,12 @@ void frame64_base(const nqs_ctx *c, const int8_t *spins, int64_t cB, int64_t b0,
                   hipStream_t s);
 void frame64_conn(const nqs_ctx *c, const int8_t *spins, const uint32_t *queue,
                   const int64_t *offsets, int64_t cap, int64_t cB, int64_t b0, int64_t nb,
-                  const void *cache, const double *site, const int32_t *neg, const double *f,
-                  double *dlog, int8_t *isign, hipStream_t s);
+                  const void *cache, const double *site, const int32_t *neg, double *dlog,
+                  int8_t *isign, hipStream_t s);
+// for the ratios of block networks by regions: NaN where a sample's zero lies
+// outside an item's region (energies: f of launch_energy_reduce)
+void frame64_zeros(const nqs_ctx *c, const uint32_t *queue, const int64_t *offsets, int64_t cap,
+                   int64_t B, const double *site, const double *f, double *dlog, hipStream_t s);
 // n_steps Metropolis steps of B chains, one launch (rnd, un: [n_steps][B])
 bool frame64_chains_ok(const nqs_ctx *c);
 void frame64_chains(const nqs_ctx *c, int8_t *spins, int64_t B, int n_steps, const uint32_t *rnd,
@@ -476,10 +479,12 @@ bool tune_store(const std::string &path, const std::string &key, nqs_mode mode, 
 int mfma_full_variants(const nqs_ctx *c, int *nw, int *maxt, int cap);
 
 // --- energy / SR kernels (k_energy.hip, k_sr.hip) ---
-// isign (may be null): per-item sign ratio of the network (CNN1)
+// isign (may be null): per-item sign ratio of the network (CNN1); f (may be
+// null): log-amplitudes, not finite ones making their sample's energy NaN
 void launch_energy_reduce(const nqs_ctx *c, const int8_t *spins, int B, const int64_t *offsets,
                           const uint32_t *queue, const double *dlog, const int8_t *isign,
-                          const double *ediag, double *e_loc, int32_t *err, hipStream_t s);
+                          const double *ediag, const double *f, double *e_loc, int32_t *err,
+                          hipStream_t s);
 
 // --- CNN1 network family (k_cnn1.hip), FP64 ---
 int64_t cnn1_params(int Kb, int C);
