@@ -145,6 +145,7 @@ struct TileSite {
 };
 
 constexpr int kQuarters = 1;         // room for quarter tiles (FP64)
+constexpr int kMaxSites = 1280;      // of a frame (eight waves of ten tiles)
 
 // Accumulators of N tiles of 16 sites (NH column blocks each), of which the
 // last is formed only when `last`, and of nq <= kQuarters quarter tiles of 4
@@ -301,7 +302,11 @@ k_frame64(FrameArgs a)
     constexpr int G = W / NHB;                       // tile groups
     static_assert(G >= 1 && G * NHB == W, "waves split into column blocks and tile groups");
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    __shared__ double red[W];
+    // sums of the output terms of 64 sites (CNN2: 16), in the order of the sites:
+    // the same parts and the same order whatever W is, which depends on the number
+    // of items for 16 channels (ONE: it does not, and a wave's terms are one part)
+    constexpr bool ONE = C == 32 && NET != kNetCnn2;
+    __shared__ double red[W == 1 ? 1 : (NET == kNetCnn2 ? kMaxSites / 16 : kMaxSites / 64)];
     __shared__ int nred[W];
     const int pk = PK > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
     unsigned char *fr = lds + pk * a.lds;
@@ -653,21 +658,33 @@ k_frame64(FrameArgs a)
         }
 
         // the output neurons: per-site terms, against the sample's
-        double dl = 0.0;
-        int dn = 0;
+        double total = 0.0;
+        int dn = 0, parts = 0;
         auto take = [&](int site, double v, int neg) {
             const int64_t o = (int64_t)s * N + site;
             if constexpr (BASE) {
                 a.site[o] = v;
-                dl += v;
                 if constexpr (NET != kNetLnCosh) a.neg[o] = neg, dn += neg;
+                return v;
             } else if constexpr (CHAIN) {
                 hn[site] = v;
-                dl += v - hs[site];
+                return v - hs[site];
             } else {
-                dl += v - a.site[o];
                 if constexpr (NET != kNetLnCosh) dn += neg - a.neg[o];
+                return v - a.site[o];
             }
+        };
+        // parts i ..: the lanes' terms t in a fixed tree (lanes apart by `from` and more)
+        auto part_sum = [&](int i, auto &t, auto from) {
+#pragma unroll
+            for (int off = 32; off >= decltype(from)::value; off >>= 1)
+#pragma unroll
+                for (double &x : t) x += __shfl_xor(x, off);
+            for (double &x : t)
+                if constexpr (W == 1)
+                    total += x;
+                else if (lane == 0)
+                    red[i] = x;
         };
         if constexpr (NET == kNetCnn2) {
             if constexpr (BASE)
@@ -677,8 +694,9 @@ k_frame64(FrameArgs a)
             const int nl = r.w * r.h;
             const uint32_t mul = ((1u << 20) + r.w - 1) / r.w;
             const int pt = tid & 3;
-            for (int p0 = 0; p0 < nl; p0 += NT / 4) {
-                const int p = min(p0 + (tid >> 2), nl - 1);
+            parts = (nl + 15) >> 4;
+            for (int p0 = wave * 16; p0 < nl; p0 += NT / 4) {
+                const int p = min(p0 + (lane >> 2), nl - 1);
                 const int v = (int)(((uint32_t)p * mul) >> 20);
                 const int fx = inside(r.x0 + p - v * r.w), fy = inside(r.y0 + v);
                 double y = 0.0;
@@ -697,12 +715,16 @@ k_frame64(FrameArgs a)
                 y += __shfl_xor(y, 1);
                 y += __shfl_xor(y, 2);
                 y += fw[9 * C];
-                if (pt == 0 && p0 + (tid >> 2) < nl) take(site_of(fx, fy), log(fabs(y)), y < 0.0);
+                double t[1] = {0.0};
+                if (pt == 0 && p0 + (lane >> 2) < nl) t[0] = take(site_of(fx, fy), log(fabs(y)), y < 0.0);
+                part_sum(p0 >> 4, t, std::integral_constant<int, 4>{});
             }
         } else {
             const Region r = region(S);
+            const int nl = r.w * r.h;
             const uint32_t mul = ((1u << 20) + r.w - 1) / r.w;
-            for (int p = tid; p < r.w * r.h; p += NT) {
+            // one site's term
+            auto term = [&](int p) {
                 const int v = (int)(((uint32_t)p * mul) >> 20);
                 const int fx = inside(r.x0 + p - v * r.w), fy = inside(r.y0 + v);
                 const unsigned char *q = fr + (fy * P + fx) * 16;
@@ -724,7 +746,7 @@ k_frame64(FrameArgs a)
                             }
                         }
                     }
-                    take(site_of(fx, fy), hs, 0);
+                    return take(site_of(fx, fy), hs, 0);
                 } else {
                     LogProd lp;
                     int neg = 0;
@@ -735,26 +757,49 @@ k_frame64(FrameArgs a)
                         lp.mul(h.y);
                         neg += (h.x < 0.0) + (h.y < 0.0);
                     }
-                    take(site_of(fx, fy), lp.log(), neg);
+                    return take(site_of(fx, fy), lp.log(), neg);
+                }
+            };
+            if constexpr (ONE) {
+                double t[1] = {0.0};
+                for (int p = tid; p < nl; p += NT) t[0] += term(p);
+                part_sum(wave, t, std::integral_constant<int, 1>{});
+            } else {
+                parts = (nl + 63) >> 6;
+                // (one wave: two parts' trees at a time)
+                constexpr int PT = W == 1 ? 2 : 1;
+#pragma unroll 1
+                for (int p0 = wave * 64; p0 < nl; p0 += PT * NT) {
+                    double t[PT];
+#pragma unroll
+                    for (int i = 0; i < PT; ++i)
+                        t[i] = p0 + 64 * i + lane < nl ? term(p0 + 64 * i + lane) : 0.0;
+                    part_sum(p0 >> 6, t, std::integral_constant<int, 1>{});
                 }
             }
         }
-        // fixed-order sums over the lanes, then over the waves
-        for (int off = 32; off > 0; off >>= 1) {
-            dl += __shfl_xor(dl, off);
-            if constexpr (NET != kNetLnCosh) dn += __shfl_xor(dn, off);
-        }
-        if constexpr (W > 1) {
-            if (lane == 0) {
-                red[wave] = dl;
-                if constexpr (NET != kNetLnCosh) nred[wave] = dn;
-            }
+        if constexpr (NET != kNetLnCosh) {
+            for (int off = 32; off > 0; off >>= 1) dn += __shfl_xor(dn, off);
+            if constexpr (W > 1)
+                if (lane == 0) nred[wave] = dn;
         }
         sync();                              // the frame is free again
+        auto sum_parts = [&] {               // (four loads at a time)
+            double v = total;
+            if constexpr (W > 1 && ONE)
+                for (int i = 0; i < W; ++i) v += red[i];
+            else if constexpr (W > 1)
+                for (int i = 0; i < parts; i += 4) {
+                    double t[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) t[j] = red[min(i + j, parts - 1)];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) v += i + j < parts ? t[j] : 0.0;
+                }
+            return v;
+        };
         if constexpr (CHAIN) {
-            double v = W > 1 ? 0.0 : dl;
-            if constexpr (W > 1)
-                for (int w = 0; w < W; ++w) v += red[w];
+            const double v = sum_parts();
             if (tid == 0 && !isfinite(v)) atomicOr(a.err, kErrNonFinite);
             if (__builtin_amdgcn_readfirstlane(step < 0 || un < exp(2.0 * v))) {
                 for (int p = tid; p < N; p += NT) hs[p] = hn[p];
@@ -772,13 +817,10 @@ k_frame64(FrameArgs a)
             continue;
         }
         if (tid == 0) {
-            double v = W > 1 ? 0.0 : dl;
+            const double v = sum_parts();
             int ng = W > 1 ? 0 : dn;
-            if constexpr (W > 1)
-                for (int w = 0; w < W; ++w) {
-                    v += red[w];
-                    if constexpr (NET != kNetLnCosh) ng += nred[w];
-                }
+            if constexpr (W > 1 && NET != kNetLnCosh)
+                for (int w = 0; w < W; ++w) ng += nred[w];
             if (!isfinite(v)) atomicOr(a.err, kErrNonFinite);
             const int8_t sg = (ng & 1) ? -1 : 1;
             if constexpr (BASE) {
@@ -808,7 +850,7 @@ inline size_t frame_lds(const nqs_ctx *c, int P, bool chains = false)
     return (n + 15) & ~(size_t)15;
 }
 
-constexpr size_t kLdsMax = 160 * 1024 - 512;
+constexpr size_t kLdsMax = 160 * 1024 - 1024;   // (the part sums are beside the frame)
 
 // layers' reach: the last stencil's region is the box widened by this much
 inline int frame_reach(const nqs_ctx *c)

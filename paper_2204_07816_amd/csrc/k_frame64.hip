@@ -23,16 +23,24 @@ void launch_any(const nqs_ctx *c, const FrameArgs &a, int mode, int64_t items, i
 
 // The first shape whose waves can form every tile of the largest region at
 // once and of which the LDS holds at least eight waves on a CU (two per SIMD).
-int frame_shape(const nqs_ctx *c, int P, bool regions)
+// A few configurations (of which about half of a queue's room are there) end
+// sooner with four waves each: up to four per CU, CNN1, whose waves form both
+// column blocks, up to two and a half (one sample: ln cosh 10x10, 4 layers of
+// 16, room 400: 82 -> 65 us, 14x14, room 784: 119 -> 107, five 10x10 samples,
+// room 2000: 88 -> 94; CNN1 10x10, 6 blocks, 400: 240 -> 166, 6x6, 3 blocks,
+// 576: 89 -> 88, 1008: 94 -> 109).
+int frame_shape(const nqs_ctx *c, int P, bool regions, int64_t items)
 {
     const int C = frame_ch(c);
     const int T = frame_tiles(c, regions);
     const FrameShape *sh = C == 16 ? kShapes16 : kShapes32;
     const int ns = C == 16 ? 4 : 3;
+    const int64_t few = (c->net == kNetCnn1 ? 5 : 8) * (int64_t)c->n_cu / 2;
     for (int i = 0; i < ns - 1; ++i) {
         if (c->net == kNetCnn1 && i == 1) continue;      // (not built: two column blocks per wave)
         if (T > frame_room(c, sh[i].W, sh[i].NMAX)) continue;
         if ((int)(kLdsMax / (frame_lds(c, P) * sh[i].PK)) * sh[i].W * sh[i].PK < 8) continue;
+        if (sh[i].W == 1 && items < few) continue;
         return i;
     }
     return ns - 1;
@@ -150,7 +158,7 @@ bool frame64_pad_wins(const nqs_ctx *c, int64_t cap)
 
 bool frame64_suits(const nqs_ctx *c)
 {
-    return frame_shape(c, std::min(c->L, 2 * frame_reach(c) + 4), true) < 3;
+    return frame_shape(c, std::min(c->L, 2 * frame_reach(c) + 4), true, INT64_MAX) < 3;
 }
 
 bool cone64_ok(const nqs_ctx *c)
@@ -215,7 +223,7 @@ void frame64_conn(const nqs_ctx *c, const int8_t *spins, const uint32_t *queue,
     a.regions = cache ? 1 : 0;
     a.P = cache ? std::min(c->L, 2 * a.F + 2) : c->L;
     const int64_t items = offsets ? cap : nb;
-    launch_any(c, a, kItems, items, frame_shape(c, a.P, cache != nullptr), s);
+    launch_any(c, a, kItems, items, frame_shape(c, a.P, cache != nullptr, items), s);
 }
 
 bool frame64_chains_ok(const nqs_ctx *c)

@@ -1,0 +1,41 @@
+"""Few configurations: a sample's log ratios are the same bits alone (four waves
+a configuration) and in a large batch (one wave)."""
+import pytest
+import torch
+
+from paper_2204_07816_amd import inputs, nqs
+
+pytestmark = pytest.mark.gpu
+
+
+def make(net, L, K, C, dtype="fp64"):
+    if net == "cnn1":
+        return nqs.Context.cnn1(L, 1.0, 0.5, K, C, inputs.cnn1_weights(K, C, 0.05, 31, 1.0))
+    if net == "cnn2":
+        return nqs.Context.cnn2_tj(L, 1.0, 0.4, K, C, inputs.cnn2_weights(K, C, 1.0, 31, 2.0))
+    return nqs.Context(L, 1.0, 0.5, K, C, inputs.stress_weights(K, C, 1.0, 31), dtype)
+
+
+def spins(net, L, B):
+    return inputs.spins_tj(L, B, 2 * (L * L // 16), 32) if net == "cnn2" else inputs.spins_sz0(L, B, 32)
+
+
+@pytest.mark.parametrize("net,L,K,C,dtype,B", [
+    ("ln", 4, 2, 16, "fp64", 70), ("ln", 10, 4, 16, "fp64", 9), ("ln", 10, 4, 16, "fp32", 9),
+    ("ln", 14, 4, 16, "fp64", 5), ("ln", 16, 3, 16, "fp32", 5), ("ln", 10, 4, 8, "fp64", 9),
+    ("ln", 20, 9, 16, "fp64", 3), ("cnn1", 6, 3, 16, "fp64", 20), ("cnn1", 12, 2, 16, "fp64", 6),
+    ("cnn2", 4, 2, 16, "fp64", 80), ("cnn2", 12, 1, 16, "fp64", 12), ("cnn2", 8, 2, 16, "fp64", 20),
+])
+def test_one_sample_and_a_batch(net, L, K, C, dtype, B):
+    ctx = make(net, L, K, C, dtype)
+    sp = torch.as_tensor(spins(net, L, B)).cuda()
+    for mode in ("auto", "full"):
+        counts, offs, *_ = ctx.connected(sp)
+        n = offs.cpu().numpy()
+        many = ctx.log_ratios(sp, mode=mode)[:n[-1]]
+        e = ctx.local_energy(sp, mode=mode)
+        for b in (0, B // 2, B - 1):
+            one = ctx.log_ratios(sp[b:b + 1].contiguous(), mode=mode)[:n[b + 1] - n[b]]
+            assert torch.equal(one, many[n[b]:n[b + 1]]), (mode, b)
+            assert torch.equal(ctx.local_energy(sp[b:b + 1].contiguous(), mode=mode), e[b:b + 1])
+    assert ctx.get_error() == 0
