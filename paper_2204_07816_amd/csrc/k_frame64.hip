@@ -144,10 +144,19 @@ bool frame64_pad_ok(const nqs_ctx *c)
 // share of the lattice (FP64, 8 channels: 24x24, 5 layers, share 0.12: 17.9 ->
 // 4.6 ms; 10x10, 4 layers, 0.54: 7.1 -> 5.0 ms; 4 channels, 6x6, 2 layers,
 // 0.72: 0.31 against 0.50 ms).  Short queues are bound by launches, of which
-// the frame needs two (4x4, 2 layers of 4, 4096 pairs: 62 -> 50 us).
+// the frame needs two, and by the latency of one configuration, which the
+// frame's 16 channels cost whatever C is: from five channels on it leads (one
+// sample, 10x10, 5 layers of 8: 160 -> 78 us; 16x16, 4 layers of 6: 171 -> 96),
+// with three or four on small lattices only (room 256 of 8x8, 4 layers of 4: 69
+// -> 57 us, 4096: 86 against 105; one sample of 16x16: 80 against 94), and with
+// few channels the share's rule holds from a queue of some length on (16x16, 4
+// layers of 4, room 2048: 97 against 115 us, 4096: 145 -> 115).
 bool frame64_pad_wins(const nqs_ctx *c, int64_t cap)
 {
-    if (cap <= (int64_t)16 * c->n_cu) return true;
+    const int64_t cu = c->n_cu;
+    const int64_t room = c->C >= 5 || (c->C >= 3 && c->N <= 16) ? 16 : (c->C >= 3 && c->N <= 100 ? 4 : 0);
+    if (cap <= room * cu) return true;
+    if (c->C <= 4 && cap * c->C < 36 * cu) return false;
     double inc = 0.0;
     for (int l = 1; l <= c->K; ++l) {
         const double e = std::min(2 + 2 * l, c->L);

@@ -3,13 +3,7 @@ count, depth, network and precision, a network that it accepts has at most as
 many tiles in a layer as the widest workgroup shape forms (eight waves of ten
 tiles, split over the 16-channel column blocks), for the base pass, exchanged
 configurations and chains."""
-import os
-import subprocess
-
-import pytest
-
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-PKG = os.path.join(ROOT, "paper_2204_07816_amd")
+import host_program
 
 SOURCE = r"""
 #include <cstdio>
@@ -45,16 +39,6 @@ int main()
 
 
 def test_accepted_networks_fit_the_widest_shape(tmp_path):
-    lib = os.path.join(PKG, "libnqs.so")
-    if not os.path.exists(lib):
-        pytest.fail("libnqs.so is not built: run __graft_entry__.build()")
-    src, exe = tmp_path / "room.hip", tmp_path / "room"
-    src.write_text(SOURCE)
-    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    r = subprocess.run([hipcc, "--offload-host-only", "-std=c++17", "-O1", "-I",
-                        os.path.join(PKG, "csrc"), str(src), "-o", str(exe),
-                        "-L" + PKG, "-l:libnqs.so", "-Wl,-rpath," + PKG], capture_output=True, text=True)
-    assert r.returncode == 0, r.stderr
-    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
-    print(r.stdout[-2000:])
-    assert r.returncode == 0
+    rc, out = host_program.run(tmp_path, SOURCE)
+    print(out[-2000:])
+    assert rc == 0
