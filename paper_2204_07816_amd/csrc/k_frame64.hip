@@ -1,5 +1,7 @@
 // k_frame64.hip -- host side of the FP64 frame form (frame64.h): which networks
 // it serves, the frame and workgroup shape of a launch.
+#include <cmath>
+
 #include "frame64.h"
 
 namespace nqs {
@@ -247,6 +249,38 @@ bool frame64_pad_chains(const nqs_ctx *c, int64_t B)
 {
     return frame64_pad_ok(c) && frame_fits(c, true) &&
            (B <= (int64_t)8 * c->n_cu || frame64_pad_wins(c, B));
+}
+
+// A call of n steps is n + 1 evaluations of the torus by the one CU that holds
+// a chain (the first gives the terms of its configuration).  Step by step, few
+// chains are spread over the whole chip, in a time that hardly depends on the
+// lattice; `grown` is how it has grown at B chains (32x32, 8 layers of 16: 1, 64
+// and 256 chains 209, 255, 540 us; 20x20, 4 layers of 32: 182, 212, 295).
+// `share` is the time of one evaluation against such a step, fitted to FP64
+// measurements of few chains (us of a step, 1, 2, 4 and 8 steps a call, against
+// step by step):
+//   16 channels, 4 layers: 20x20 103 73 57 48 / 92; 30x30 181 131 106 94 / 97
+//   32 channels, 4 layers: 16x16 164 122 99 86 / 168; 22x22 290 213 175 155 / 180
+//   CNN1, 3 blocks: 16x16 108 77 61 54 / 130; 20x20 166 120 98 86 / 140
+// The step-by-step form costs half as much again without a cone, almost twice
+// as much in FP32, and with 3 or 4 and fewer channels less than with 16.
+bool frame64_chains_pay(const nqs_ctx *c, int64_t B, int n_steps, bool cone)
+{
+    const bool wide = frame_ch(c) == 32, pad = frame_ch(c) != c->C;
+    const double fill = (double)B / std::max(c->n_cu, 1);
+    const double grown = 1.0 + (c->C <= 4 ? 0.75 : 1.5) * c->N / 1024 * fill * std::sqrt(fill);
+    double share = wide ? (c->N + 150) / 820.0 : (c->N + 180) / 1150.0;
+    if (c->net == kNetCnn1)
+        share = (c->N + 250) / 1250.0 * (cone ? 1.0 : 0.92);
+    else if (c->net == kNetCnn2)
+        share *= wide ? 0.83 : 0.74;
+    else if (pad)
+        share *= wide ? 0.92 : (c->C >= 5 ? 0.8 : (c->C >= 3 ? 1.45 : 2.0));
+    else if (c->dtype == NQS_FP32)
+        share *= 0.55;
+    else if (!cone)
+        share *= 0.68;
+    return (n_steps + 1.0) * share <= n_steps * grown;
 }
 
 void frame64_chains(const nqs_ctx *c, int8_t *spins, int64_t B, int n_steps, const uint32_t *rnd,

@@ -271,10 +271,10 @@ nqs_mode resolve_mode(const nqs_ctx *c, nqs_mode m)
 // neurons that an exchange can change may be recomputed and the others taken
 // from the base pass (the same values): FP64 and FP32 networks whose planes fit
 // the LDS, and BF16 networks that the incremental kernels serve, unless their
-// own timing chose FULL.
+// own timing chose FULL.  `layered`: FULL by a launch per layer.
 struct Form {
     nqs_mode mode;
-    bool regions;
+    bool regions, layered = false;
 };
 
 Form resolve_form(const nqs_ctx *c, nqs_mode m)
@@ -497,7 +497,7 @@ nqs_status log_ratio_stage(nqs_ctx *c, const int8_t *spins, int B, Form form,
     Workspace &w = c->ws;
     const nqs_mode mode = form.mode;
     NQS_TRY(ensure(w.fbase, sizeof(double) * std::max(B, 1), s));
-    if (mode == NQS_FULL &&
+    if (mode == NQS_FULL && !form.layered &&
         (frame64_ok(c) || (form.regions && frame64_pad_ok(c) && frame64_pad_wins(c, cap))))
         return frame_ratio_stage(c, spins, B, form.regions, offsets, dlog, cap, s);
     if (const BlockNet *bn = block_net(c))
@@ -1204,14 +1204,19 @@ nqs_status nqs_mcmc(nqs_ctx *c, int8_t *spins, int64_t B, int32_t n_steps,
     hipStream_t s = (hipStream_t)stream;
     c->last_stream = s;
     if (B == 0 || n_steps == 0 || bonds_per_sample(c) == 0) return NQS_OK;
-    const Form form = resolve_form(c, mode);
+    Form form = resolve_form(c, mode);
     const nqs_mode m = form.mode;
     if (m == NQS_INCREMENTAL && c->dtype == NQS_BF16X3 && !incremental_ok(c))
         return NQS_E_UNSUPPORTED;
     if (frame64_chains_ok(c) || frame64_pad_chains(c, B)) {
-        // FP64: every step in one launch (the forms give the same ratios)
-        frame64_chains(c, spins, B, n_steps, rand_bond, rand_u, accepted, s);
-        return finish_call();
+        // FP64 and FP32: every step in one launch (the forms give the same
+        // ratios), also under capture, since it needs no workspace
+        const bool cone = m == NQS_INCREMENTAL && incremental_ok(c);
+        if (frame64_chains_pay(c, B, n_steps, cone) || stream_capturing(s)) {
+            frame64_chains(c, spins, B, n_steps, rand_bond, rand_u, accepted, s);
+            return finish_call();
+        }
+        if (!cone) form = Form{NQS_FULL, false, true};
     }
     Workspace &w = c->ws;
     NQS_TRY(ensure(w.queue, sizeof(uint32_t) * B, s));

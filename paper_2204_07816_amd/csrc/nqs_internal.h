@@ -359,8 +359,10 @@ void frame64_conn(const nqs_ctx *c, const int8_t *spins, const uint32_t *queue,
 // outside an item's region (energies: f of launch_energy_reduce)
 void frame64_zeros(const nqs_ctx *c, const uint32_t *queue, const int64_t *offsets, int64_t cap,
                    int64_t B, const double *site, const double *f, double *dlog, hipStream_t s);
-// n_steps Metropolis steps of B chains, one launch (rnd, un: [n_steps][B])
+// n_steps Metropolis steps of B chains, one launch (rnd, un: [n_steps][B]);
+// frame64_chains_pay: faster so than step by step (cone: with the incremental form)
 bool frame64_chains_ok(const nqs_ctx *c);
+bool frame64_chains_pay(const nqs_ctx *c, int64_t B, int n_steps, bool cone);
 void frame64_chains(const nqs_ctx *c, int8_t *spins, int64_t B, int n_steps, const uint32_t *rnd,
                     const double *un, int32_t *accepted, hipStream_t s);
 // Backward: O[B][P] from the saved activations and tanh of the pre-activations.

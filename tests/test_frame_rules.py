@@ -43,3 +43,41 @@ int main()
 }
 """ % rows)
     assert rc == 0, out
+
+
+def test_chains_of_few_steps(tmp_path):
+    """(network, L, K, C, precision, chains, steps, cone) and whether one launch
+    for all steps was measured to be the faster form, by at least 5%."""
+    ln, c1, c2 = 0, 1, 2
+    cases = [
+        (ln, 10, 4, 16, 0, 1, 1, 0, 1), (ln, 16, 4, 32, 0, 256, 1, 1, 1), (ln, 24, 4, 16, 0, 1, 1, 1, 0),
+        (ln, 24, 4, 16, 0, 16, 8, 1, 1), (ln, 24, 4, 16, 0, 256, 1, 1, 1), (ln, 28, 4, 16, 0, 16, 2, 1, 0),
+        (ln, 32, 8, 16, 0, 16, 4, 1, 0), (ln, 32, 8, 16, 0, 256, 1, 1, 1), (ln, 20, 4, 32, 0, 1, 1, 1, 0),
+        (ln, 20, 4, 32, 0, 16, 8, 1, 1), (ln, 22, 4, 32, 0, 16, 2, 1, 0), (ln, 24, 6, 32, 0, 1, 4, 1, 0),
+        (ln, 24, 6, 32, 0, 64, 8, 1, 1), (ln, 24, 6, 32, 0, 256, 1, 1, 1), (ln, 24, 12, 32, 0, 1, 1, 0, 0),
+        (ln, 24, 12, 32, 0, 1, 2, 0, 1), (ln, 30, 12, 16, 0, 1, 1, 0, 0), (ln, 20, 4, 32, 1, 1, 1, 0, 1),
+        (ln, 34, 4, 16, 1, 1, 1, 0, 0), (ln, 34, 4, 16, 1, 1, 2, 0, 1), (ln, 30, 2, 16, 1, 16, 1, 0, 0), (ln, 30, 4, 4, 0, 1, 8, 0, 0),
+        (ln, 30, 4, 2, 0, 128, 8, 0, 0), (ln, 20, 4, 4, 0, 1, 1, 0, 0), (ln, 20, 4, 4, 0, 1, 8, 0, 1),
+        (ln, 30, 2, 8, 0, 1, 1, 0, 0), (ln, 30, 2, 8, 0, 1, 8, 0, 1), (ln, 30, 4, 4, 0, 128, 8, 0, 0),
+        (c1, 16, 3, 16, 0, 1, 1, 1, 1), (c1, 28, 2, 16, 0, 1, 2, 1, 0), (c1, 32, 2, 16, 0, 256, 2, 1, 1),
+        (c1, 30, 8, 16, 0, 1, 4, 0, 0), (c2, 14, 4, 16, 0, 1, 1, 0, 1), (c2, 28, 2, 16, 0, 64, 2, 0, 1),
+        (c2, 22, 6, 32, 0, 1, 1, 0, 0), (c2, 22, 6, 32, 0, 32, 8, 0, 1),
+    ]
+    rows = ",".join("{%d,%d,%d,%d,%d,%d,%d,%d,%d}" % c for c in cases)
+    rc, out = host_program.run(tmp_path, HEAD + r"""
+int main()
+{
+    const int t[][9] = {%s};
+    int bad = 0;
+    for (auto &r : t) {
+        const nqs_ctx c = net(r[0], r[1], r[2], r[3], r[4] ? NQS_FP32 : NQS_FP64);
+        if (frame64_chains_pay(&c, r[5], r[6], r[7] != 0) != (r[8] != 0)) {
+            ++bad;
+            std::printf("net %%d L %%d K %%d C %%d chains %%d steps %%d: %%d\n", r[0], r[1], r[2], r[3],
+                        r[5], r[6], !r[8]);
+        }
+    }
+    return bad;
+}
+""" % rows)
+    assert rc == 0, out

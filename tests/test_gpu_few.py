@@ -1,5 +1,8 @@
 """Few configurations: a sample's log ratios are the same bits alone (four waves
-a configuration) and in a large batch (one wave)."""
+a configuration) and in a large batch (one wave), and a run of Metropolis steps
+gives the same chains in one call (all steps in one launch) and a step a call
+(step by step on large lattices)."""
+import numpy as np
 import pytest
 import torch
 
@@ -39,3 +42,47 @@ def test_one_sample_and_a_batch(net, L, K, C, dtype, B):
             assert torch.equal(one, many[n[b]:n[b + 1]]), (mode, b)
             assert torch.equal(ctx.local_energy(sp[b:b + 1].contiguous(), mode=mode), e[b:b + 1])
     assert ctx.get_error() == 0
+
+
+@pytest.mark.parametrize("net,L,K,C,dtype", [
+    ("ln", 24, 2, 32, "fp64"), ("ln", 20, 9, 16, "fp64"), ("ln", 22, 11, 32, "fp64"),
+    ("ln", 34, 2, 16, "fp32"), ("ln", 34, 2, 16, "fp64"), ("ln", 30, 2, 4, "fp64"),
+    ("ln", 24, 2, 20, "fp64"), ("ln", 30, 2, 3, "fp32"), ("cnn1", 20, 3, 16, "fp64"),
+    ("cnn1", 20, 5, 16, "fp64"), ("cnn2", 22, 1, 32, "fp64"), ("cnn2", 28, 1, 16, "fp64"),
+])
+@pytest.mark.parametrize("mode", ["auto", "full"])
+def test_one_call_and_a_call_a_step(net, L, K, C, dtype, mode):
+    B, steps = 3, 24
+    ctx = make(net, L, K, C, dtype)
+    sp = spins(net, L, B)
+    rb, ru = (torch.as_tensor(x).cuda() for x in inputs.mcmc_randoms(77, 0, steps, B))
+    one, each = torch.as_tensor(sp.copy()).cuda(), torch.as_tensor(sp.copy()).cuda()
+    acc = ctx.mcmc(one, rb, ru, mode=mode)
+    acc2 = torch.zeros_like(acc)
+    for t in range(steps):
+        ctx.mcmc(each, rb[t:t + 1], ru[t:t + 1], accepted=acc2, mode=mode)
+    assert torch.equal(one, each) and torch.equal(acc, acc2)
+    assert 0 < int(acc.sum()) < B * steps
+    assert ctx.get_error() == 0
+
+
+@pytest.mark.parametrize("net,L,K,C,dtype", [("ln", 24, 2, 32, "fp64"), ("ln", 30, 2, 4, "fp64"),
+                                             ("cnn1", 20, 3, 16, "fp64")])
+def test_captured_step_needs_no_workspace(net, L, K, C, dtype):
+    """A captured call of one step allocates nothing, whatever the lattice."""
+    B = 2
+    ctx = make(net, L, K, C, dtype)
+    sp = spins(net, L, B)
+    rb, ru = (torch.as_tensor(x).cuda() for x in inputs.mcmc_randoms(79, 0, 1, B))
+    rb = rb.to(torch.int32)
+    s = torch.as_tensor(sp.copy()).cuda()
+    acc = torch.zeros(B, dtype=torch.int32, device="cuda")
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        ctx.mcmc(s, rb, ru, accepted=acc)
+    eager, acc2 = torch.as_tensor(sp.copy()).cuda(), torch.zeros_like(acc)
+    for _ in range(3):
+        g.replay()
+        make(net, L, K, C, dtype).mcmc(eager, rb, ru, accepted=acc2)
+        torch.cuda.synchronize()
+        assert torch.equal(s, eager) and torch.equal(acc, acc2)
