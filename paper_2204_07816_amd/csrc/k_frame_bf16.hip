@@ -173,7 +173,8 @@ k_frame_bf16(BfJobs jobs)
         }
     };
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    __shared__ double red[W];
+    __shared__ double red[W == 8 ? W : 1];
+    double *terms = (double *)(lds + jobs.lds);      // four waves: [tiles][16] of the last layer
     const int pk = PK > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
     unsigned char *fr = lds + pk * jobs.lds;
     const int tid = PK > 1 ? threadIdx.x & 63 : threadIdx.x, lane = tid & 63;
@@ -349,6 +350,9 @@ k_frame_bf16(BfJobs jobs)
         ring(1);
         sync();
 
+        // Last layer: one wave and four give the same sum, since the choice depends
+        // on the launch's other configurations.  The one wave adds its lanes' tiles
+        // in order, then the lanes in a tree; of four, the first does so from LDS.
         double fsum = 0.0;
         for (int k = 2; k <= K; ++k) {
             const Region r = region(k);
@@ -409,8 +413,13 @@ k_frame_bf16(BfJobs jobs)
                             sum += __shfl_xor(sum, 16);
                             sum += __shfl_xor(sum, 32);
                             const int f = to[T0 + t] >> 4, fy = f / P;
+                            double d = 0.0;
                             if (g == 0 && f < P * P)
-                                fsum += sum - a.hsum[(int64_t)s * N0 + lat(fy, ay) * L + lat(f - fy * P, ax)];
+                                d = sum - a.hsum[(int64_t)s * N0 + lat(fy, ay) * L + lat(f - fy * P, ax)];
+                            if constexpr (W != 4)
+                                fsum += d;
+                            else if (g == 0)
+                                terms[(wave + W * (T0 + t)) * 16 + n16] = d;
                         }
                     }
                 };
@@ -439,8 +448,16 @@ k_frame_bf16(BfJobs jobs)
             sync();
         }
 
-        for (int off = 32; off > 0; off >>= 1) fsum += __shfl_xor(fsum, off);
-        if constexpr (W > 1) {
+        if constexpr (W == 4) {
+            const Region r = region(K);
+            const int T = (r.w * r.h + 15) >> 4;
+            if (tid < 16)
+#pragma unroll 4
+                for (int t = 0; t < T; ++t) fsum += terms[t * 16 + tid];
+        }
+        if (W != 4 || wave == 0)
+            for (int off = 32; off > 0; off >>= 1) fsum += __shfl_xor(fsum, off);
+        if constexpr (W == 8) {
             if (lane == 0) red[wave] = fsum;
             __syncthreads();
             fsum = 0.0;
@@ -468,7 +485,7 @@ template <int C, int W, int PK, int NMAX, int EU, bool FEW = false>
 void launch_w(const BfJobs &jobs, int n_cu, int64_t items, hipStream_t s)
 {
     const auto kernel = k_frame_bf16<C, W, PK, NMAX, EU, FEW>;
-    const int lds = jobs.lds * PK;
+    const int lds = jobs.lds * PK + (W == 4 ? W * NMAX * 16 * (int)sizeof(double) : 0);
     (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     int occ = 1;
     (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, W * PK * 64, lds);
@@ -488,7 +505,15 @@ bool mfma_inc_supported(const nqs_ctx *c)
            2 * (size_t)(e * e) * (c->C * 2 + 16) <= 160 * 1024 - 1024;
 }
 
-void mfma_inc_forward_jobs(const ConnJob *jobs, int n, hipStream_t s)
+// tiles of a lattice's last layer
+static int last_tiles(const nqs_ctx *c)
+{
+    const int w = std::min(c->L, 2 + 2 * c->K);
+    return (w * w + 15) / 16;
+}
+
+// one launch: lattices of at most 24 tiles, or of more
+static void inc_launch(const ConnJob *jobs, int n, hipStream_t s)
 {
     if (n <= 0) return;
     BfJobs jp{};
@@ -514,8 +539,7 @@ void mfma_inc_forward_jobs(const ConnJob *jobs, int n, hipStream_t s)
         p.K = c->K;
         p.P = frame_side(c);
         lds = std::max(lds, frame_bytes(c));
-        const int w = std::min(c->L, 2 + 2 * c->K);
-        tiles = std::max(tiles, (w * w + 15) / 16);
+        tiles = std::max(tiles, last_tiles(c));
         items += jobs[i].capacity;
     }
     if (items <= 0) return;
@@ -551,6 +575,19 @@ void mfma_inc_forward_jobs(const ConnJob *jobs, int n, hipStream_t s)
         else
             launch_w<16, 8, 1, 11, 2>(jp, n_cu, items, s);
     }
+}
+
+void mfma_inc_forward_jobs(const ConnJob *jobs, int n, hipStream_t s)
+{
+    // lattices of more than 24 tiles by a launch of their own: their eight waves
+    // would sum the others' terms in another order than their single calls
+    ConnJob part[2][kMaxConnJobs];
+    int m[2] = {0, 0};
+    for (int i = 0; i < n; ++i) {
+        const int big = last_tiles(jobs[i].c) > 24;
+        part[big][m[big]++] = jobs[i];
+    }
+    for (int b = 0; b < 2; ++b) inc_launch(part[b], m[b], s);
 }
 
 }  // namespace nqs

@@ -1,0 +1,40 @@
+"""Several lattices in one launch of the BF16 frame kernel: every lattice's
+energies are its single-lattice call's, bit for bit, also where the launch's
+workgroup shape (set by the largest lattice and all queues) is not the single
+call's; and a sample's ratios do not depend on its batch."""
+import pytest
+import torch
+
+from paper_2204_07816_amd import inputs, nqs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("K,C,lattices", [
+    (4, 32, ((8, 1), (12, 40), (20, 8))),        # four waves alone, one in the launch
+    (3, 16, ((6, 1), (8, 2), (16, 30))),
+    (9, 16, ((12, 30), (14, 2), (24, 6))),       # 9 and 13 tiles alone, 25 in the launch
+    (7, 32, ((10, 20), (12, 1), (16, 12))),      # 7 and 9 tiles alone, 16 in the launch
+])
+def test_each_lattice_equals_its_own_call(K, C, lattices):
+    w = inputs.stress_weights(K, C, 1.0, 93)
+    ctx = [nqs.Context(L, 1.0, 0.5, K, C, w, "bf16") for L, _ in lattices]
+    sps = [torch.as_tensor(inputs.spins_any(L, B, 94)).cuda() for L, B in lattices]
+    es = [torch.empty(B, dtype=torch.float64, device="cuda") for _, B in lattices]
+    nqs.local_energy_multi(list(zip(ctx, sps, es)), mode="incremental")
+    for c, sp, e in zip(ctx, sps, es):
+        assert torch.equal(e, c.local_energy(sp, mode="incremental")), c.L
+        assert c.get_error() == 0
+
+
+@pytest.mark.parametrize("L,K,C,B", [(4, 2, 16, 70), (8, 3, 32, 30), (10, 4, 16, 30), (12, 6, 32, 20),
+                                     (14, 5, 16, 9), (16, 7, 32, 9), (24, 9, 16, 3)])
+def test_one_sample_and_a_batch(L, K, C, B):
+    ctx = nqs.Context(L, 1.0, 0.5, K, C, inputs.stress_weights(K, C, 1.0, 95), "bf16")
+    sp = torch.as_tensor(inputs.spins_any(L, B, 96)).cuda()
+    counts, offs, *_ = ctx.connected(sp)
+    n = offs.cpu().numpy()
+    many = ctx.log_ratios(sp, mode="incremental")[:n[-1]]
+    for b in (0, B // 2, B - 1):
+        one = ctx.log_ratios(sp[b:b + 1].contiguous(), mode="incremental")[:n[b + 1] - n[b]]
+        assert torch.equal(one, many[n[b]:n[b + 1]]), b
