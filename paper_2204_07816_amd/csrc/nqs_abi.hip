@@ -284,17 +284,14 @@ Form resolve_form(const nqs_ctx *c, nqs_mode m)
     return Form{r, m == NQS_AUTO && r == NQS_FULL && can};
 }
 
-// The kernel family of a BF16 exchanged pass of at most `cap` configurations.
-// Regions pay even where they cover the torus (10x10, 8 layers of 32 channels,
-// 256 samples: 3.41 -> 1.11 ms; 4x4, 2 layers, 2048 samples: 0.71 -> 0.19 ms),
-// because one wave per configuration needs no barriers.  With few
-// configurations the workgroup per configuration of FULL ends sooner (8x8, 6
-// layers of 16 channels, one sample, at most 256 configurations: 44 us against
-// 55; four samples: 55 either way), so the line lies at four per CU.
-nqs_mode bf16_conn_mode(const nqs_ctx *c, Form f, int64_t cap)
-{
-    return f.regions && cap >= (int64_t)4 * c->n_cu ? NQS_INCREMENTAL : f.mode;
-}
+// The kernel family of a BF16 exchanged pass.  Regions pay even where they cover
+// the torus (10x10, 8 layers of 32 channels, 256 samples: 3.41 -> 1.11 ms; 4x4, 2
+// layers, 2048 samples: 0.71 -> 0.19 ms), because one wave per configuration
+// needs no barriers, and for few configurations with four waves each (one to six
+// samples: 8x8, 6 layers of 16: 42 to 59 -> 41 to 47 us; 12x12, 7 of 16: 77 to 150
+// -> 63 to 81; 4x4 and 6x6 within 2 us either way).  The choice does not depend on
+// the batch, whose size would show in a sample's last bits.
+nqs_mode bf16_conn_mode(Form f) { return f.regions ? NQS_INCREMENTAL : f.mode; }
 
 #define NQS_TRY(x)                        \
     do {                                  \
@@ -527,7 +524,7 @@ nqs_status log_ratio_stage(nqs_ctx *c, const int8_t *spins, int B, Form form,
             (void)hipEventCreate(&e1);
             (void)hipEventRecord(e0, s);
         }
-        mfma_conn_forward(c, bf16_conn_mode(c, form, cap), spins, (uint32_t *)w.queue.ptr, (int64_t *)w.qlen.ptr, cap,
+        mfma_conn_forward(c, bf16_conn_mode(form), spins, (uint32_t *)w.queue.ptr, (int64_t *)w.qlen.ptr, cap,
                           (double *)w.hsum.ptr, w.cache.ptr, dlog, nullptr, s);
         if (c->timing) {
             (void)hipEventRecord(e1, s);
@@ -1241,6 +1238,10 @@ nqs_status nqs_mcmc(nqs_ctx *c, int8_t *spins, int64_t B, int32_t n_steps,
         }
         return finish_call();
     }
+    // BF16: on the smallest lattices few chains step faster by FULL (20 steps: 4x4, 64
+    // chains, 294 against 312 us, 6x6, 4 layers of 32, 100 chains, 517 against 539;
+    // 10x10, 8 layers, 1195 against 1113)
+    if (c->dtype == NQS_BF16 && c->N <= 36 && B < (int64_t)4 * c->n_cu) form.regions = false;
     // BF16: a chain's base pass is repeated only after a step that moved it (14x14,
     // 5 layers of 16, 357 chains: the base pass was 35 us of a step's 58)
     int32_t *moved = nullptr;
@@ -1312,8 +1313,7 @@ nqs_status nqs_local_energy_multi(const nqs_eloc_job *jobs, int32_t n, nqs_mode 
         int k = 0;
         for (int i = 0; i <= n; ++i) {
             nqs_ctx *c = i < n ? jobs[i].ctx : nullptr;
-            if (c && jobs[i].B > 0 &&
-                bf16_conn_mode(c, resolve_form(c, mode), bonds_per_sample(c) * jobs[i].B) == m) {
+            if (c && jobs[i].B > 0 && bf16_conn_mode(resolve_form(c, mode)) == m) {
                 cj[k++] = ConnJob{c, jobs[i].spins, (const uint32_t *)c->ws.queue.ptr,
                                   (const int64_t *)c->ws.qlen.ptr, bonds_per_sample(c) * jobs[i].B,
                                   (const double *)c->ws.hsum.ptr, c->ws.cache.ptr,

@@ -27,14 +27,15 @@ def test_each_lattice_equals_its_own_call(K, C, lattices):
         assert c.get_error() == 0
 
 
-@pytest.mark.parametrize("L,K,C,B", [(4, 2, 16, 70), (8, 3, 32, 30), (10, 4, 16, 30), (12, 6, 32, 20),
+@pytest.mark.parametrize("L,K,C,B", [(4, 2, 16, 70), (8, 3, 32, 30), (8, 6, 16, 30), (10, 8, 32, 9), (10, 4, 16, 30), (12, 6, 32, 20),
                                      (14, 5, 16, 9), (16, 7, 32, 9), (24, 9, 16, 3)])
 def test_one_sample_and_a_batch(L, K, C, B):
     ctx = nqs.Context(L, 1.0, 0.5, K, C, inputs.stress_weights(K, C, 1.0, 95), "bf16")
     sp = torch.as_tensor(inputs.spins_any(L, B, 96)).cuda()
     counts, offs, *_ = ctx.connected(sp)
     n = offs.cpu().numpy()
-    many = ctx.log_ratios(sp, mode="incremental")[:n[-1]]
-    for b in (0, B // 2, B - 1):
-        one = ctx.log_ratios(sp[b:b + 1].contiguous(), mode="incremental")[:n[b + 1] - n[b]]
-        assert torch.equal(one, many[n[b]:n[b + 1]]), b
+    for mode in ("incremental", "auto", "full"):
+        many = ctx.log_ratios(sp, mode=mode)[:n[-1]]
+        for b in (0, B // 2, B - 1):
+            one = ctx.log_ratios(sp[b:b + 1].contiguous(), mode=mode)[:n[b + 1] - n[b]]
+            assert torch.equal(one, many[n[b]:n[b + 1]]), (mode, b)
