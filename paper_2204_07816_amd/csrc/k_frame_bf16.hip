@@ -173,8 +173,9 @@ k_frame_bf16(BfJobs jobs)
         }
     };
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    constexpr bool PARTS = W == 4 || FEW;            // more waves than one for up to 24 tiles
     __shared__ double red[W == 8 ? W : 1];
-    double *terms = (double *)(lds + jobs.lds);      // four waves: [tiles][16] of the last layer
+    double *terms = (double *)(lds + jobs.lds);      // PARTS: [tiles][16] of the last layer
     const int pk = PK > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
     unsigned char *fr = lds + pk * jobs.lds;
     const int tid = PK > 1 ? threadIdx.x & 63 : threadIdx.x, lane = tid & 63;
@@ -350,9 +351,10 @@ k_frame_bf16(BfJobs jobs)
         ring(1);
         sync();
 
-        // Last layer: one wave and four give the same sum, since the choice depends
-        // on the launch's other configurations.  The one wave adds its lanes' tiles
-        // in order, then the lanes in a tree; of four, the first does so from LDS.
+        // Last layer: one wave and several give the same sum, since the choice
+        // depends on the launch's other configurations.  The one wave adds its lanes'
+        // tiles in order, then the lanes in a tree; of several, the first does so
+        // from LDS (up to 24 tiles; beyond, always eight waves, each for itself).
         double fsum = 0.0;
         for (int k = 2; k <= K; ++k) {
             const Region r = region(k);
@@ -416,7 +418,7 @@ k_frame_bf16(BfJobs jobs)
                             double d = 0.0;
                             if (g == 0 && f < P * P)
                                 d = sum - a.hsum[(int64_t)s * N0 + lat(fy, ay) * L + lat(f - fy * P, ax)];
-                            if constexpr (W != 4)
+                            if constexpr (!PARTS)
                                 fsum += d;
                             else if (g == 0)
                                 terms[(wave + W * (T0 + t)) * 16 + n16] = d;
@@ -448,16 +450,16 @@ k_frame_bf16(BfJobs jobs)
             sync();
         }
 
-        if constexpr (W == 4) {
+        if constexpr (PARTS) {
             const Region r = region(K);
             const int T = (r.w * r.h + 15) >> 4;
             if (tid < 16)
 #pragma unroll 4
                 for (int t = 0; t < T; ++t) fsum += terms[t * 16 + tid];
         }
-        if (W != 4 || wave == 0)
+        if (!PARTS || wave == 0)
             for (int off = 32; off > 0; off >>= 1) fsum += __shfl_xor(fsum, off);
-        if constexpr (W == 8) {
+        if constexpr (W == 8 && !PARTS) {
             if (lane == 0) red[wave] = fsum;
             __syncthreads();
             fsum = 0.0;
@@ -485,7 +487,7 @@ template <int C, int W, int PK, int NMAX, int EU, bool FEW = false>
 void launch_w(const BfJobs &jobs, int n_cu, int64_t items, hipStream_t s)
 {
     const auto kernel = k_frame_bf16<C, W, PK, NMAX, EU, FEW>;
-    const int lds = jobs.lds * PK + (W == 4 ? W * NMAX * 16 * (int)sizeof(double) : 0);
+    const int lds = jobs.lds * PK + (W == 4 || FEW ? W * NMAX * 16 * (int)sizeof(double) : 0);
     (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     int occ = 1;
     (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, W * PK * 64, lds);
@@ -552,11 +554,18 @@ static void inc_launch(const ConnJob *jobs, int n, hipStream_t s)
     // four (1600 configurations) 65 and 70
     const bool one = tiles <= 16 && 8 * lds <= kLdsMax && items >= (int64_t)4 * n_cu;
     const bool few = tiles <= 24 && items < (int64_t)4 * n_cu;
+    // eight where each has a CU to itself: what chains wait for in every step is one
+    // configuration's latency (20 steps of 100 chains: 12x12, 5 layers of 16, 792 ->
+    // 758 us, 12x12, 8 layers, 1117 -> 1064; 357 chains of 14x14 1081 and 1079, 900
+    // 1780 and 1950)
+    const bool lone = few && items <= n_cu;
     if (jobs[0].c->C == 32) {
         if (one && tiles <= 9)
             launch_w<32, 1, 4, 9, 3>(jp, n_cu, items, s);
         else if (one)
             launch_w<32, 1, 4, 16, 2>(jp, n_cu, items, s);
+        else if (lone)
+            launch_w<32, 8, 1, 3, 2, true>(jp, n_cu, items, s);
         else if (few)
             launch_w<32, 4, 1, 6, 3, true>(jp, n_cu, items, s);
         else if (tiles <= 24)
@@ -568,6 +577,8 @@ static void inc_launch(const ConnJob *jobs, int n, hipStream_t s)
             launch_w<16, 1, 4, 9, 4>(jp, n_cu, items, s);
         else if (one)
             launch_w<16, 1, 4, 16, 3>(jp, n_cu, items, s);
+        else if (lone)
+            launch_w<16, 8, 1, 3, 4, true>(jp, n_cu, items, s);
         else if (few)
             launch_w<16, 4, 1, 6, 4, true>(jp, n_cu, items, s);
         else if (tiles <= 24)

@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("K,C,lattices", [
     (4, 32, ((8, 1), (12, 40), (20, 8))),        # four waves alone, one in the launch
-    (3, 16, ((6, 1), (8, 2), (16, 30))),
+    (3, 16, ((6, 1), (8, 2), (16, 30))),         # eight waves alone
     (9, 16, ((12, 30), (14, 2), (24, 6))),       # 9 and 13 tiles alone, 25 in the launch
     (7, 32, ((10, 20), (12, 1), (16, 12))),      # 7 and 9 tiles alone, 16 in the launch
 ])
