@@ -270,8 +270,9 @@ nqs_mode resolve_mode(const nqs_ctx *c, nqs_mode m)
 // Where a requested mode leads.  `regions`: FULL reached by AUTO where the
 // neurons that an exchange can change may be recomputed and the others taken
 // from the base pass (the same values): FP64 and FP32 networks whose planes fit
-// the LDS, and BF16 networks that the incremental kernels serve, unless their
-// own timing chose FULL.  `layered`: FULL by a launch per layer.
+// the LDS, and BF16 networks that the incremental kernels serve.  Where the
+// autotuner (or its file) chose FULL over INCREMENTAL, AUTO is the form that it
+// timed, the whole torus.  `layered`: FULL by a launch per layer.
 struct Form {
     nqs_mode mode;
     bool regions, layered = false;
@@ -280,8 +281,9 @@ struct Form {
 Form resolve_form(const nqs_ctx *c, nqs_mode m)
 {
     const nqs_mode r = resolve_mode(c, m);
-    const bool can = c->dtype == NQS_BF16 ? (!c->tuned && incremental_ok(c)) : (frame64_ok(c) || frame64_pad_ok(c));
-    return Form{r, m == NQS_AUTO && r == NQS_FULL && can};
+    const bool inc = incremental_ok(c);
+    const bool can = c->dtype == NQS_BF16 ? inc : frame64_ok(c) || frame64_pad_ok(c);
+    return Form{r, m == NQS_AUTO && r == NQS_FULL && can && !(c->tuned && inc)};
 }
 
 // The kernel family of a BF16 exchanged pass.  Regions pay even where they cover
