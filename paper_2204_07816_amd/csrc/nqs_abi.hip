@@ -388,6 +388,14 @@ int64_t frame_chunk(const nqs_ctx *c, int64_t B)
                                     (int64_t)(((size_t)4 << 30) / frame64_cache_bytes(c, 1)), B));
 }
 
+// Whether the activation cache of regions is there or may be allocated: under
+// capture AUTO makes do with what was reserved, and a reservation for FULL has no
+// cache (the whole torus, or the layered form, needs none).
+bool regions_room(nqs_ctx *c, int64_t B, hipStream_t s)
+{
+    return !stream_capturing(s) || c->ws.cache.bytes >= frame64_cache_bytes(c, frame_chunk(c, B));
+}
+
 nqs_status frame_reserve(nqs_ctx *c, int64_t B, int64_t cap, bool regions, hipStream_t s)
 {
     Workspace &w = c->ws;
@@ -496,9 +504,11 @@ nqs_status log_ratio_stage(nqs_ctx *c, const int8_t *spins, int B, Form form,
     Workspace &w = c->ws;
     const nqs_mode mode = form.mode;
     NQS_TRY(ensure(w.fbase, sizeof(double) * std::max(B, 1), s));
-    if (mode == NQS_FULL && !form.layered &&
-        (frame64_ok(c) || (form.regions && frame64_pad_ok(c) && frame64_pad_wins(c, cap))))
-        return frame_ratio_stage(c, spins, B, form.regions, offsets, dlog, cap, s);
+    if (mode == NQS_FULL && !form.layered) {
+        const bool regions = form.regions && regions_room(c, B, s);
+        if (frame64_ok(c) || (regions && frame64_pad_ok(c) && frame64_pad_wins(c, cap)))
+            return frame_ratio_stage(c, spins, B, regions, offsets, dlog, cap, s);
+    }
     if (const BlockNet *bn = block_net(c))
         return block_ratio_stage(c, bn, spins, B, mode, offsets, dlog, cap, s);
     NQS_TRY(ensure(w.hsum, sizeof(double) * (size_t)std::max(B, 1) * c->N, s));
@@ -985,11 +995,10 @@ nqs_status nqs_reserve(nqs_ctx *c, int64_t B_max, nqs_mode mode)
     NQS_TRY(ensure(w.dlog, sizeof(double) * std::max<int64_t>(cap, 1), s));
     NQS_TRY(ensure(w.fbase, sizeof(double) * std::max(B, 1), s));
     NQS_TRY(ensure(w.hsum, sizeof(double) * (size_t)std::max(B, 1) * c->N, s));
-    // the frame form serves FULL and AUTO: both reserve its buffers, and the
-    // planes are then those of the amplitudes alone
-    const bool frame = frame64_ok(c);
-    if (frame) NQS_TRY(frame_reserve(c, B, cap, resolve_mode(c, mode) == NQS_FULL, s));
-    if (mode == NQS_AUTO && frame64_pad_ok(c)) NQS_TRY(frame_reserve(c, B, cap, true, s));
+    // the frame form serves FULL and AUTO (which also keeps activations): both
+    // reserve its buffers, and the planes are then those of the amplitudes alone
+    const bool frame = frame64_ok(c), regions = resolve_form(c, mode).regions;
+    if (frame || (regions && frame64_pad_ok(c))) NQS_TRY(frame_reserve(c, B, cap, regions, s));
     const int64_t work = frame ? B : std::max<int64_t>(cap, B);
     if (const BlockNet *bn = block_net(c)) {
         const int64_t chunk = bn->chunk(c, work);
