@@ -81,7 +81,8 @@ typedef enum {
 
 /* Arithmetic of the convolutions of layers 2..K:
  *   FP64      plain double precision (the paper's);
- *   FP32      single precision on the vector ALU;
+ *   FP32      single precision, fused multiply-adds over the input channels
+ *             in order (vector ALU, or FP32 matrix cores, the same values);
  *   BF16      matrix cores, BF16 operands (weights and activations rounded to
  *             nearest even), FP32 accumulation;
  *   BF16X3    matrix cores, split BF16: every operand x is carried as a pair
@@ -103,7 +104,16 @@ typedef enum { NQS_FP64 = 0, NQS_FP32 = 1, NQS_BF16 = 2, NQS_BF16X3 = 3 } nqs_dt
  * neuron with the full pass's arithmetic, in the same order, so the two
  * differ only in the order of the final sum over sites; its cache holds
  * layers 1 .. K-1 of the samples, (K-1) B N C doubles (at most 16 GiB per
- * fill: larger batches are taken in chunks of samples). */
+ * fill: larger batches are taken in chunks of samples).
+ * Where AUTO resolves to FULL (nqs_auto_mode) without the autotuner having
+ * chosen it over INCREMENTAL, it may still take the neurons that an exchange
+ * cannot change from the base pass, of FP64 and FP32 networks that fit the LDS
+ * (at most 4 GiB of activations per fill) and BF16 networks: the neurons are
+ * FULL's, only the final sum's order differs.  A sample's ratios do not depend
+ * on the other samples of the call in FULL and INCREMENTAL, and in AUTO for
+ * BF16, 16 and 32 channels and the block networks; for FP64 and FP32 networks of
+ * other channel counts AUTO chooses by the length of the queue, and the last
+ * bits may follow. */
 typedef enum { NQS_AUTO = 0, NQS_FULL = 1, NQS_INCREMENTAL = 2 } nqs_mode;
 
 typedef struct {
@@ -111,7 +121,7 @@ typedef struct {
     int32_t channels;       /* C                                              */
     int32_t marshall_sign;  /* 1: psi carries the Marshall sign; 0: psi > 0   */
     nqs_dtype conv_dtype;   /* arithmetic of the convolutions: FP64 (plain),
-                               FP32 (vector), BF16 (MFMA, FP32 accumulate)   */
+                               FP32 (plain), BF16 (MFMA, FP32 accumulate)    */
 } nqs_cnn_spec;
 
 /* Create a context for one lattice and network on the current HIP device.
@@ -259,9 +269,10 @@ nqs_status nqs_set_weights_device(nqs_ctx *ctx, const double *theta, void *strea
 nqs_status nqs_get_weights(nqs_ctx *ctx, double *weights, int64_t n);
 
 /* Pre-allocate workspace for batches up to B_max in the given mode (AUTO:
- * the mode AUTO resolves to now; the incremental forms' activation caches
- * are reserved when the mode is INCREMENTAL), so that later calls allocate
- * nothing (and may be captured into a hipGraph).                          */
+ * the mode AUTO resolves to now), so that later calls allocate nothing (and
+ * may be captured into a hipGraph).  The FP64 and FP32 activation caches are
+ * reserved for INCREMENTAL, and for AUTO where it keeps activations (see
+ * nqs_mode), not for FULL; AUTO under capture without one recomputes in full. */
 nqs_status nqs_reserve(nqs_ctx *ctx, int64_t B_max, nqs_mode mode);
 
 /* log|psi(s)| (FP64 [B]) and the sign of psi (int8 [B], may be NULL)
@@ -363,8 +374,10 @@ nqs_status nqs_log_ratios(nqs_ctx *ctx, const int8_t *spins, int64_t B,
  * chains sample |psi|^2.  rand_bond: device uint32 [n_steps][B]; rand_u:
  * device FP64 [n_steps][B] in [0, 1); accepted (device int32 [B], may be
  * NULL) is increased by each chain's accepted exchanges.  f(S') - f(S) is
- * computed as nqs_local_energy computes it, in `mode`.  No coupling: no
- * move.  Errors as nqs_local_energy.                                       */
+ * computed as nqs_local_energy computes it, in `mode`, to the order of the
+ * sums: whether the steps share one launch is chosen by the numbers of chains
+ * and steps (one launch under capture, where the network fits the LDS).  No
+ * coupling: no move.  Errors as nqs_local_energy.                          */
 nqs_status nqs_mcmc(nqs_ctx *ctx, int8_t *spins, int64_t B, int32_t n_steps,
                     const uint32_t *rand_bond, const double *rand_u,
                     int32_t *accepted, nqs_mode mode, void *stream);
@@ -376,7 +389,8 @@ nqs_status nqs_mcmc(nqs_ctx *ctx, int8_t *spins, int64_t B, int32_t n_steps,
  * per context) and one kernel family share one persistent launch over their
  * concatenated queues (up to 8 lattices per launch; in incremental mode the
  * lattices with unwrapped cones share the cone kernel and the others the
- * general incremental kernel), then each lattice's FP64 ratio sums are
+ * frame kernel, of these the ones of more than 24 tiles of 16 sites
+ * another launch), then each lattice's FP64 ratio sums are
  * taken, so every lattice's energies equal its single-lattice call's.
  * FP64 / FP32 contexts and CNN1 / CNN2 contexts (every job of one network
  * family) run lattice after lattice.  Errors as nqs_local_energy, checked

@@ -1,12 +1,12 @@
-// frame64.h -- the FP64 networks (ln cosh CNN, CNN1, CNN2) evaluated whole
-// in LDS: one workgroup takes a configuration through every layer on a frame
+// frame64.h -- the FP64 networks (ln cosh CNN, CNN1, CNN2) and the FP32 ln cosh
+// CNN evaluated whole in LDS: one workgroup takes a configuration through every layer on a frame
 // of P x P sites and C channels, so no activation of an exchanged
 // configuration [Sec. 5.4.1] touches HBM.
 //
 // The layered form (k_conv_f64mma.hip) writes and re-reads a plane per layer;
 // its matrix cores wait on A operands gathered from memory, 16 cache lines
 // per load, and each layer ends in the tail of a launch.  Here the frame is
-// kept as C / 2 planes of 16-byte channel pairs, an odd number of chunks
+// kept as C / 2 planes of 16-byte channel pairs (FP32: C / 4 of quads), an odd number of chunks
 // apart, so the 16 sites of an operand fetch are 256 contiguous bytes of LDS
 // (no bank conflicts) and the two chunks of a lane sit at constant offsets.
 //
@@ -23,9 +23,9 @@
 // at once, so one fetch of the weights serves up to NMAX tiles and the MFMAs
 // of different tiles are independent.  The sums wait in registers until every
 // wave has read the frame, and are then stored; ln cosh is applied to the
-// stored values by the wave that stored them, in a rolled loop.  Operand
-// layout, packed taps and MFMA order are k_conv_mma's, so every neuron equals
-// the layered form's bit for bit.
+// accumulators meanwhile.  Operand layout, packed taps and MFMA order are
+// k_conv_mma's (FP32: the vector kernels' order), so every neuron equals the
+// layered form's bit for bit.
 #pragma once
 
 #include <algorithm>

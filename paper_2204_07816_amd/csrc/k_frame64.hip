@@ -1,5 +1,6 @@
-// k_frame64.hip -- host side of the FP64 frame form (frame64.h): which networks
-// it serves, the frame and workgroup shape of a launch.
+// k_frame64.hip -- host side of the FP64 and FP32 frame form (frame64.h): which
+// networks it serves, the frame and workgroup shape of a launch; and the look at
+// a sample's zeros outside an item's region (k_frame_zeros).
 #include <cmath>
 
 #include "frame64.h"

@@ -11,8 +11,9 @@
 //   accept:  a pair of different values (antiparallel spins; t-J also an
 //            electron and a hole) is exchanged when u < exp(2 (f(S') - f(S))),
 //            u the caller's uniform number in [0, 1).
-// FP64 networks whose planes fit the LDS run all their steps in one launch
-// (k_frame64.hip); what follows serves the others.
+// FP64 and FP32 networks whose planes fit the LDS run all their steps in one
+// launch (k_frame64.hip), except few chains of few steps on large lattices; what
+// follows serves those and the other networks.
 // Where the incremental cone kernel serves, the base pass is taken once and
 // then kept current: accepted chains run a write-back pass of the cone kernel
 // (their cone's activations and site sums replace the cached ones, which is

@@ -9,8 +9,9 @@
 // (alpha, beta, r.r) stay on the device, so the solve never synchronises
 // with the host and can be captured in a graph.  All reductions are two-stage
 // with a fixed order (deterministic), the same for every launch shape.  One
-// iteration is four launches (Obar p, the partial column sums of Obar^T u, Ap
-// with p.Ap, the update of x and r), three where P is small; each finishes the
+// iteration is five launches (p, from the second one on; Obar p; the partial
+// column sums of Obar^T u; Ap with p.Ap; the update of x and r), three where P is
+// small (k_ap_small is p, the column sums and Ap in one); each finishes the
 // previous one's reduction itself (see k_rowdot).
 #include <algorithm>
 

@@ -410,7 +410,7 @@ nqs_status frame_reserve(nqs_ctx *c, int64_t B, int64_t cap, bool regions, hipSt
     return NQS_OK;
 }
 
-// FP64 networks whole in LDS: per chunk of samples the base pass and the
+// FP64 and FP32 networks whole in LDS: per chunk of samples the base pass and the
 // chunk's queue items (offsets null: one item per sample).
 nqs_status frame_ratio_stage(nqs_ctx *c, const int8_t *spins, int B, bool regions,
                              const int64_t *offsets, double *dlog, int64_t cap, hipStream_t s)
@@ -1218,7 +1218,7 @@ nqs_status nqs_mcmc(nqs_ctx *c, int8_t *spins, int64_t B, int32_t n_steps,
         return NQS_E_UNSUPPORTED;
     if (frame64_chains_ok(c) || frame64_pad_chains(c, B)) {
         // FP64 and FP32: every step in one launch (the forms give the same
-        // ratios), also under capture, since it needs no workspace
+        // neurons), also under capture, since it needs no workspace
         const bool cone = m == NQS_INCREMENTAL && incremental_ok(c);
         if (frame64_chains_pay(c, B, n_steps, cone) || stream_capturing(s)) {
             frame64_chains(c, spins, B, n_steps, rand_bond, rand_u, accepted, s);

@@ -84,8 +84,11 @@ __device__ inline double expm1_m2(double a)
 // for the library expm1 and a split logarithm.  FP64 matrix and vector
 // instructions of a SIMD do not overlap (measured: 64 and 5 cycles each, 149
 // for one MFMA and 16 vector instructions of two waves), so this count is time.
-// Error against long double: at most 2.7 ulp of |z| (2.7 before), 0.27 to
-// 0.59 ulp rms over 1e-8 .. 700 (0.20 to 0.63 before).
+// Error against long double, ulp of |z|, rms (library expm1 and the split
+// logarithm in brackets): to 0.1 0.54 (0.60), .. 0.35 0.56 to 0.59 (0.58 to
+// 0.61), .. 0.5 0.64 (0.73), .. 0.7 0.35 (0.44), .. 1 0.49 (0.47), .. 1.5 0.29
+// (0.23), .. 2 0.42 (0.37), .. 3 0.27 (0.25), above 0.29 to 0.37 (0.28 to 0.37);
+// at most 2.6 (2.8).
 __device__ inline double ln_cosh_of(double a, double m)
 {
     const double den = 4.0 + m;
@@ -326,7 +329,7 @@ bool cone64_ok(const nqs_ctx *c);
 int64_t cone64_chunk(const nqs_ctx *c, int64_t B);
 void vec_base_forward_cached(const nqs_ctx *c, const int8_t *spins, int nb, double *f,
                              double *hsum, void *plane, double *cache, int64_t cB, hipStream_t s);
-// FP64 networks whole in LDS (k_frame64.hip): 16 or 32 channels (CNN1: 16),
+// FP64 and FP32 networks whole in LDS (k_frame64.hip): 16 or 32 channels (CNN1: 16),
 // an L x L frame of the channels within the LDS.  The base pass of samples
 // b0 .. b0 + nb - 1 writes per site the output terms (all samples' [B][N]
 // arrays; neg, sgn: block networks), f, and, unless cache is null, the
