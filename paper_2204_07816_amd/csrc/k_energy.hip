@@ -42,7 +42,7 @@ k_energy_reduce(const int64_t *__restrict__ offsets, const uint32_t *__restrict_
     }
     if (threadIdx.x == 0) {
         double e = ediag[s] + red[0];
-        if (f) e += f[s] - f[s];
+        if (f && q0 < q1) e += f[s] - f[s];
         if (!isfinite(e)) atomicOr(err, kErrNonFinite);
         e_loc[s] = e;
     }
@@ -111,7 +111,7 @@ k_energy_reduce_tj(const int8_t *__restrict__ spins, int L, const int64_t *__res
     }
     if (threadIdx.x == 0) {
         double e = ediag[s] + red[0];
-        if (f) e += f[s] - f[s];
+        if (f && q0 < q1) e += f[s] - f[s];
         if (!isfinite(e)) atomicOr(err, kErrNonFinite);
         e_loc[s] = e;
     }

@@ -485,7 +485,7 @@ int mfma_full_variants(const nqs_ctx *c, int *nw, int *maxt, int cap);
 
 // --- energy / SR kernels (k_energy.hip, k_sr.hip) ---
 // isign (may be null): per-item sign ratio of the network (CNN1); f (may be
-// null): log-amplitudes, not finite ones making their sample's energy NaN
+// null): log-amplitudes, not finite ones making the energy of a sample with items NaN
 void launch_energy_reduce(const nqs_ctx *c, const int8_t *spins, int B, const int64_t *offsets,
                           const uint32_t *queue, const double *dlog, const int8_t *isign,
                           const double *ediag, const double *f, double *e_loc, int32_t *err,

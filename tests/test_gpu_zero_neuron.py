@@ -49,3 +49,19 @@ def test_zero_outside_the_region(at):
         assert ctx.get_error() == NONFINITE
         assert not np.isfinite(ctx.local_energy(sp, mode=mode).cpu().numpy()).any()
         assert ctx.get_error() == NONFINITE
+
+
+@pytest.mark.parametrize("tj", [False, True])
+def test_zero_amplitude_without_exchanges(tj):
+    """All spins up: neurons of 0, but no configuration to compare with, so the
+    energy is the diagonal part (spins: 72 bonds of (J1 + J2) / 4; t-J: 0)."""
+    L, C = 6, 16
+    w = cnn1_weights(C)
+    ctx = nqs.Context.cnn1_tj(L, 1.0, 0.4, 1, C, w) if tj else nqs.Context.cnn1(L, 1.0, 0.5, 1, C, w)
+    sp = torch.ones((1, L, L), dtype=torch.int8, device="cuda")
+    got = []
+    for mode in ("full", "auto"):
+        e = float(ctx.local_energy(sp, mode=mode)[0])
+        assert e == (0.0 if tj else 27.0), mode
+        got.append(ctx.get_error())
+    assert got[0] == got[1]
